@@ -149,10 +149,11 @@ void ii_plan_free(ii_plan_t* plan);
  * segments' bytes, packed, when it has gaps between segments), copy it to a
  * device slot with one hipMemcpyAsync, then scatter it into its tensors
  * with the device kernel. A pinned blob's chunk skips the host slot: it is
- * copied straight from the blob -- its used range in one copy, or, when it
- * has gaps, its run groups in one 1-D or 2-D copy each (see
- * ii_plan_copy_bytes; a chunk of many groups that is mostly gaps is still
- * gathered through the host slot).
+ * copied straight from the blob. A pinned blob whose table has gaps between
+ * segments, or at most 16 chunks, skips the chunks altogether: one launch on
+ * `stream` reads the blob over the host link, as ii_load_device does from
+ * pinned memory (a traced load runs the chunks all the same, its chunks with
+ * gaps moved as ii_plan_copy_bytes says).
  * Chunks holding no segment are not touched. Chunk k's copy and scatter
  * run on lane k mod lanes (see ii_plan_set_ring), so with two or more lanes
  * chunk k+1's copy overlaps chunk k's scatter. A slot is
@@ -228,8 +229,10 @@ int ii_load_file(ii_plan_t* plan, int fd, uint64_t file_bytes, void* const* dst_
  *                [dev_image + lo, + hi) must lie inside one device allocation
  *                or in pinned host memory (checked, II_EINVAL). From pinned
  *                host memory the kernel reads the blob over the host link
- *                itself: no ring and no copy engine, one launch -- the
- *                lowest latency for small loads.
+ *                itself: no ring and no copy engine, one launch of at most
+ *                256 workgroups that walk the windows in order -- the
+ *                lowest latency for small loads, and the link's rate for
+ *                large ones.
  *   image_bytes  size of the image; must be >= the plan's span end hi.
  *   dst_ptrs     as for ii_load; must not overlap [dev_image, +hi).
  *   stream       the kernel runs on this stream, after the work already on
@@ -307,8 +310,8 @@ int ii_switch(const ii_plan_t* plan_old, ii_plan_t* plan_new, void* arena, uint6
               const void* host_blob_new, uint64_t blob_bytes, hipStream_t stream);
 
 /*
- * Ring configuration, before the plan's first load or after
- * ii_plan_release. depth = number of chunk slots in flight (1..8; default 3
+ * Ring configuration, before the plan's first load from host memory or a
+ * file, or after ii_plan_release. depth = number of chunk slots in flight (1..8; default 3
  * or $II_RING_DEPTH); host_threads = threads that read, copy or gather
  * chunk bytes into the pinned slots (pageable blobs, files, gathered chunks;
  * 1..64; default min(8, cores) or $II_HOST_THREADS);
@@ -380,7 +383,10 @@ size_t ii_plan_num_segments(const ii_plan_t* plan);
 uint64_t ii_plan_chunk_bytes(const ii_plan_t* plan);
 uint64_t ii_plan_payload_bytes(const ii_plan_t* plan); /* sum of nbytes */
 uint64_t ii_plan_arena_bytes(const ii_plan_t* plan);
-/* bytes one ii_load from a pinned blob moves from host to device. A table
+/* bytes one load from a pinned blob moves from host to device through the
+ * chunk pipeline (ii_switch, a traced ii_load, an ii_load of a table without
+ * gaps and more than 16 chunks; an ii_load that reads the blob over the link
+ * in one launch moves payload_bytes). A table
  * whose tensors tile their span: per chunk, its used range -- first
  * segment's start to last segment's end, rounded out to 256-byte boundaries
  * inside the chunk -- copied in place (hi - lo in all). A table with gaps

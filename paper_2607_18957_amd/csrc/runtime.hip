@@ -60,6 +60,9 @@ hipError_t launch_scatter_slot(const uint8_t* slot, const TileDev* tiles, const 
 hipError_t launch_scatter_layout(const uint8_t* span, const TileDev* tiles, const uint32_t* win,
                                  uint64_t ntiles, const LayoutSeg* segs, uint32_t tile_bytes,
                                  bool mixed, hipStream_t stream);
+hipError_t launch_scatter_layout_link(const uint8_t* span, const TileDev* tiles,
+                                      const uint32_t* win, uint64_t ntiles, const LayoutSeg* segs,
+                                      uint32_t tile_bytes, hipStream_t stream);
 hipError_t launch_zero(const RangeDev* ranges, uint32_t n, hipStream_t stream);
 
 #define II_HIP(call)                                                                   \
@@ -164,6 +167,7 @@ struct Runtime {
     bool ranges_used = false;
     // ring
     uint32_t depth = 0;
+    bool ring_fixed = false;  // a load has run: its configuration may not change any more
     std::vector<uint8_t*> hslot, dslot;
     std::vector<hipEvent_t> copy_done, scatter_done;
     std::vector<char> copy_rec, scatter_rec;
@@ -425,7 +429,11 @@ static AllocInfo alloc_info(uint64_t x) {
 // allocation or one pinned host allocation (reach.h). A kernel or a DMA
 // touching pageable memory, unknown memory, or a range that runs from one
 // allocation into whatever lies past its end would fault the device.
-static bool accessible(uint64_t b, uint64_t e) { return reachable(alloc_info(b), b, e); }
+static bool accessible(uint64_t b, uint64_t e, AllocInfo* info = nullptr) {
+    const AllocInfo a = alloc_info(b);
+    if (info) *info = a;
+    return reachable(a, b, e);
+}
 
 // Destination ranges of the non-empty tensors, sorted by address, after
 // checking that each is present, aligned and disjoint from the others.
@@ -489,7 +497,7 @@ static int check_image(const ii_plan_t* p, const uint64_t* dst, uint64_t b, uint
 enum RowTables { kRingRows = 1, kLayoutRows = 2 };
 
 static int prepare_segments(ii_plan_t* p, const uint64_t* dst, hipStream_t s, uint64_t image_b,
-                            uint64_t image_e, int which) {
+                            uint64_t image_e, int which, AllocInfo* image_info = nullptr) {
     Runtime* r = p->rt;
     const size_t n = p->nbytes.size(), S = p->seg_len.size();
     const bool same = r->cached_valid && r->cached_dst.size() == n &&
@@ -506,7 +514,7 @@ static int prepare_segments(ii_plan_t* p, const uint64_t* dst, hipStream_t s, ui
     int rc = check_reach(r->cached_ranges);
     if (rc) return rc;
     if (image_e > image_b) {
-        if (!accessible(image_b, image_e))
+        if (!accessible(image_b, image_e, image_info))
             return fail(II_EINVAL, "the image's span [%#llx, %#llx) is not memory the device can "
                         "read: not inside one device allocation or one pinned host allocation",
                         (unsigned long long)image_b, (unsigned long long)image_e);
@@ -837,22 +845,71 @@ static int run_ring(ii_plan_t* p, const Source& src, const uint64_t* dst, hipStr
     return II_OK;
 }
 
-static int run_device(ii_plan_t* p, const uint8_t* image, const uint64_t* dst, hipStream_t stream) {
+// The layout kernel over an image, the span [image + lo, image + hi) in the
+// memory `from`: HBM, or pinned host memory read over the link.
+static hipError_t scatter_image(const ii_plan_t* p, const uint8_t* image, const TileDev* tiles,
+                                const uint32_t* win, const LayoutSeg* rows, AllocInfo::Kind from,
+                                hipStream_t stream) {
+    if (launch_injected()) return hipErrorLaunchFailure;
+    if (from == AllocInfo::kPinnedHost)
+        return launch_scatter_layout_link(image + p->lo, tiles, win, p->ltiles.size(), rows,
+                                          p->tile_bytes, stream);
+    return launch_scatter_layout(image + p->lo, tiles, win, p->ltiles.size(), rows, p->tile_bytes,
+                                 p->layout_mixed, stream);
+}
+
+// One launch on `stream` over the whole table. image_b..image_e: the image's
+// span when it is checked here (reachable, disjoint from the destinations),
+// empty when the caller knows it to be pinned host memory.
+static int run_image(ii_plan_t* p, const uint8_t* image, const uint64_t* dst, hipStream_t stream,
+                     uint64_t image_b, uint64_t image_e) {
     int rc = ensure_state(p);
     if (rc) return rc;
     rc = ensure_layout_tables(p);
     if (rc) return rc;
     Runtime* r = p->rt;
-    const uint64_t ib = reinterpret_cast<uint64_t>(image);
-    rc = prepare_segments(p, dst, stream, ib + p->lo, ib + p->hi, kLayoutRows);
+    AllocInfo info;
+    info.kind = AllocInfo::kPinnedHost;
+    rc = prepare_segments(p, dst, stream, image_b, image_e, kLayoutRows, &info);
     if (rc) return rc;
-    II_HIP(launch_injected() ? hipErrorLaunchFailure
-                             : launch_scatter_layout(image + p->lo, r->d_ltiles, r->d_lwin,
-                                                     p->ltiles.size(), r->d_lsegs, p->tile_bytes,
-                                                     p->layout_mixed, stream));
+    II_HIP(scatter_image(p, image, r->d_ltiles, r->d_lwin, r->d_lsegs, info.kind, stream));
     II_HIP(hipEventRecord(r->tables_idle, stream));
     r->tables_used = true;
     return II_OK;
+}
+
+static int run_device(ii_plan_t* p, const uint8_t* image, const uint64_t* dst, hipStream_t stream) {
+    const uint64_t ib = reinterpret_cast<uint64_t>(image);
+    return run_image(p, image, dst, stream, ib + p->lo, ib + p->hi);
+}
+
+// Whether a load from a pinned blob goes by one launch that reads the blob
+// over the link (scatter_layout_link) instead of the chunk pipeline:
+//   tables with gaps, always: the pipeline's 2-D copies of their rows hold
+//     the calling thread for the whole transfer, and the copy engine moves
+//     rows that are not multiples of 4 bytes one by one (one rank of four of
+//     a 3.0 GB model, 749 MB: 13.75 -> 13.04 ms; 218 MB of 8-bit weights in
+//     rows of 1659 and 3473 bytes: 219 -> 4.0 ms);
+//   others of at most kLinkChunks chunks: the pipeline's first copy and last
+//     scatter, its hand-overs and the copy engines' start-up are then a
+//     sizeable part (16.8 MB in 5 chunks: 378 -> 312 us with the host
+//     waiting, 707 -> 302 us in back-to-back loads; 200 MB in 13: 3.62 ->
+//     3.50 ms). With more chunks the two are within 1.3% (3.0 GB in 45:
+//     52.8 and 52.1 ms; 948 MB in 57, permuted: 16.9 both), and the copy
+//     engines, which prefetch before the caller's earlier work is done,
+//     stay the path.
+// A traced load always runs the pipeline whose timeline it records.
+constexpr size_t kLinkChunks = 16;
+
+static bool reads_over_link(const ii_plan_t* p) {
+    if (p->trace) return false;
+    return p->packed_distinct || p->num_chunks <= kLinkChunks;
+}
+
+static int run_pinned(ii_plan_t* p, const uint8_t* blob, const uint64_t* dst, hipStream_t stream) {
+    const int rc = run_image(p, blob, dst, stream, 0, 0);
+    if (p->rt) p->rt->ring_fixed = true;
+    return rc;
 }
 
 // ---------------------------------------------------------------------------
@@ -914,7 +971,8 @@ static int run_device_noalloc(ii_plan_t* p, const uint8_t* image, const uint64_t
     if (rc) return rc;
     if (p->ltiles.empty()) return II_OK;  // nothing to move
     const uint64_t ib = reinterpret_cast<uint64_t>(image);
-    if (!accessible(ib + p->lo, ib + p->hi))
+    AllocInfo info;
+    if (!accessible(ib + p->lo, ib + p->hi, &info))
         return fail(II_EINVAL, "the image's span [%#llx, %#llx) is not memory the device can "
                     "read: not inside one device allocation or one pinned host allocation",
                     (unsigned long long)(ib + p->lo), (unsigned long long)(ib + p->hi));
@@ -938,13 +996,10 @@ static int run_device_noalloc(ii_plan_t* p, const uint8_t* image, const uint64_t
     II_HIP(h2d(ws + l.tiles, p->ltiles.data(), p->ltiles.size() * sizeof(TileDev), stream));
     if (!p->lwin.empty())
         II_HIP(h2d(ws + l.win, p->lwin.data(), p->lwin.size() * sizeof(uint32_t), stream));
-    II_HIP(launch_injected()
-               ? hipErrorLaunchFailure
-               : launch_scatter_layout(
-                     image + p->lo, reinterpret_cast<const TileDev*>(ws + l.tiles),
-                     p->lwin.empty() ? nullptr : reinterpret_cast<const uint32_t*>(ws + l.win),
-                     p->ltiles.size(), reinterpret_cast<const LayoutSeg*>(ws + l.rows),
-                     p->tile_bytes, p->layout_mixed, stream));
+    II_HIP(scatter_image(
+        p, image, reinterpret_cast<const TileDev*>(ws + l.tiles),
+        p->lwin.empty() ? nullptr : reinterpret_cast<const uint32_t*>(ws + l.win),
+        reinterpret_cast<const LayoutSeg*>(ws + l.rows), info.kind, stream));
     return II_OK;
 }
 
@@ -1051,7 +1106,9 @@ extern "C" int ii_load(ii_plan_t* p, const void* host_blob, uint64_t blob_bytes,
     inject_arm();
     Source src;
     src.blob = static_cast<const uint8_t*>(host_blob);
-    int rc = run_ring(p, src, reinterpret_cast<const uint64_t*>(dst_ptrs), stream, nullptr);
+    const uint64_t* dst = reinterpret_cast<const uint64_t*>(dst_ptrs);
+    int rc = reads_over_link(p) && pinned_span(p, src.blob) ? run_pinned(p, src.blob, dst, stream)
+                                                            : run_ring(p, src, dst, stream, nullptr);
     return rc ? drain(p, stream, rc) : II_OK;
 }
 
@@ -1197,7 +1254,8 @@ extern "C" int ii_plan_set_ring(ii_plan_t* p, uint32_t depth, uint32_t host_thre
         copy_streams > kMaxLanes || copy_streams > depth)
         return fail(II_EINVAL, "ii_plan_set_ring: depth must be 1..8, host_threads 1..64, "
                                "copy_streams 1..min(4, depth)");
-    if (p->rt && p->rt->depth) return fail(II_EBUSY, "ii_plan_set_ring: ring already allocated");
+    if (p->rt && (p->rt->depth || p->rt->ring_fixed))
+        return fail(II_EBUSY, "ii_plan_set_ring: ring already allocated");
     p->ring_depth = depth;
     p->host_threads = host_threads;
     p->copy_streams = copy_streams;

@@ -76,6 +76,9 @@ static_assert((1ull << 32) / 1024 <= kMaxGridBlocks, "a chunk's tiles fit one la
 
 namespace {
 
+constexpr uint32_t kLinkBlocks = 256;  // workgroups of scatter_layout_link
+constexpr uint32_t kLinkRun = 4;       // consecutive tiles one of them takes at a time
+
 // Global-address-space accesses: plain pointers made from integer addresses
 // would be generic (flat) accesses, which also count against the LDS wait
 // counter.
@@ -298,6 +301,45 @@ __global__ __launch_bounds__(kBlock) void scatter_layout(
     scatter_tile<kMixed>(td.first, td.last, row_of);
 }
 
+// The same table read over the host link: `span` is pinned host memory. What
+// bounds it is the link (57.3 GB/s for a 1 GiB copy-engine copy), and how
+// many reads are in flight decides how close it gets. With one workgroup per
+// tile the whole chip's worth of reads queues at the link at once, in an
+// order that spreads over 33 MB of the blob: a launch then costs ~55 us on
+// top of its bytes (16.8 MB in 354 us, 3.0 GB at 55.6 GB/s). kLinkBlocks
+// workgroups (one per compute unit, two wavefronts each) that walk the tiles
+// front to back keep ~1 MB in flight and read a compact moving window: 16.8
+// MB in 302 us, 3.0 GB at 57.5 GB/s, and the rest of each compute unit stays
+// free for other kernels. Swept from 32 to 512 workgroups: 192 and more are
+// level, 64 too, 96 to 144 lose 4-7%, 32 loses 20%.
+//   Each workgroup takes kLinkRun consecutive tiles at a time: where source
+// and destination are not congruent, neighbouring tiles share a 128-byte
+// source line, and the one L2 that both now go through fetches it over the
+// link once (100,000 tensors in a permuted file: 54.8 GB/s with runs of 1,
+// 55.5 with 2, 56.0 with 4, 56.1 with 8; a run of 4 leaves small tables
+// spread over more workgroups).
+//   All of a tile's loads are issued before any is used: a link read takes
+// microseconds, and waits between units would double them.
+__global__ __launch_bounds__(kBlock) void scatter_layout_link(
+    const uint8_t* __restrict__ span, const TileDev* __restrict__ tiles,
+    const uint32_t* __restrict__ win, const LayoutSeg* __restrict__ segs, uint32_t tile_bytes,
+    uint32_t ntiles) {
+    const uint64_t sb = reinterpret_cast<uint64_t>(span);
+    // ntiles < 2^31 and a step is at most kLinkBlocks * kLinkRun: no wrap
+    for (uint32_t g0 = blockIdx.x * kLinkRun; g0 < ntiles; g0 += gridDim.x * kLinkRun) {
+        const uint32_t g1 = min(ntiles, g0 + kLinkRun);
+        for (uint32_t g = g0; g < g1; ++g) {
+            const TileDev td = tiles[g];
+            const uint64_t w0 = (uint64_t)(win ? win[g] : g) * tile_bytes;
+            const uint64_t w1 = w0 + tile_bytes;
+            scatter_tile<true>(td.first, td.last, [&](uint32_t s, uint32_t* cnt) {
+                const LayoutSeg ls = segs[s];
+                return make_row(ls.dst, ls.pos, ls.len, sb + ls.src - ls.pos, w0, w1, cnt);
+            });
+        }
+    }
+}
+
 // Zero the byte ranges [r.begin, r.end) (device addresses). One workgroup per
 // range; 16-byte stores for whole aligned blocks, exact narrow stores at the
 // edges.
@@ -340,6 +382,18 @@ hipError_t launch_scatter_layout(const uint8_t* span, const TileDev* tiles, cons
     else
         hipLaunchKernelGGL(scatter_layout<false>, dim3(gx, gy), dim3(kBlock), 0, stream, span,
                            tiles, win, segs, tile_bytes, (uint32_t)ntiles);
+    return hipGetLastError();
+}
+
+hipError_t launch_scatter_layout_link(const uint8_t* span, const TileDev* tiles,
+                                      const uint32_t* win, uint64_t ntiles, const LayoutSeg* segs,
+                                      uint32_t tile_bytes, hipStream_t stream) {
+    if (ntiles == 0) return hipSuccess;
+    if (ntiles > 0x7fffffffull) return hipErrorInvalidConfiguration;
+    const uint32_t blocks = (uint32_t)std::min<uint64_t>((ntiles + kLinkRun - 1) / kLinkRun,
+                                                         kLinkBlocks);
+    hipLaunchKernelGGL(scatter_layout_link, dim3(blocks), dim3(kBlock), 0, stream, span, tiles,
+                       win, segs, tile_bytes, (uint32_t)ntiles);
     return hipGetLastError();
 }
 

@@ -368,6 +368,34 @@ def test_load_from_file(orc, where, root, direct):
             os.unlink(path)
 
 
+@pytest.mark.parametrize("tiles", [1, 3, 4, 5, 1023, 1024, 1025, 2049])
+def test_pinned_blob_read_over_the_link(orc, tiles):
+    """The kernel that reads pinned host memory: at most 256 workgroups that
+    take four tiles at a time, around the sizes where a run is short, where
+    every workgroup has exactly one run and where some take a second. The
+    load of a pinned blob in up to 16 chunks takes it, with 17 the chunk
+    pipeline runs; each also fixes the ring's configuration."""
+    total = tiles * 4096 - 7
+    sizes = [total // 3 + 1, 13, total - total // 3 - 14]
+    t = oracle_pins._u8_table(sizes, [5 + sizes[1], 5, 5 + sizes[0] + sizes[1]], [1, 1, 1])
+    t.name = f"{tiles} tiles"
+    blob = synth.blob(5 + total, seed=tiles)
+    for chunks in (1, 16, 17):
+        t.chunk_bytes = max(16, -(-total // chunks) + 15 & ~15)
+        for mode in ("pinned", "image-pinned"):
+            plan = _load_arena(orc, t, mode=mode, blob=blob)
+            if mode == "pinned":
+                with pytest.raises(ii.IIError) as e:
+                    plan.set_ring(2, 2, 2)
+                assert e.value.code == ii.EBUSY
+
+
+def test_pinned_shard_of_odd_rows(orc):
+    """One rank's 8-bit weights in rows of 33 and 83 bytes, from a pinned blob."""
+    t = synth.transformer_tp("odd", 2, 264, 664, 264, 512, 3, 8, dtype="fp8_e4m3", chunk=1 << 14)
+    _load_arena(orc, t, mode="pinned")
+
+
 def test_separate_tensor_buffers(orc):
     """Destinations are independent allocations, not an arena."""
     for table in (synth.tiny(), synth.stress(n=5000)):
