@@ -116,9 +116,18 @@ struct ii_plan_s {
     // whether the image kernel runs its variant for tables of many small
     // tensors (more loads in flight; see the planner's rule)
     bool layout_mixed = false;
+    // the segments in layout order as the image kernel reads them, for any
+    // arena (dst = pos)
+    std::vector<ii::LayoutSeg> lrows;
+    // for the destination checks: the first non-empty tensor (n if none),
+    // whether there are empty ones, the end of the last non-empty tensor in
+    // the layout and the largest alignment of a non-empty one
+    size_t first_live = 0;
+    bool has_empty = false;
+    uint64_t layout_end = 0, live_align = 1;
     // host buffers of ii_load_device_noalloc, sized when the plan is made so
-    // that the call itself allocates nothing: the layout-order segment rows
-    // with resolved destinations, and the destination ranges its checks sort
+    // that the call itself allocates nothing: the layout-order rows with
+    // resolved destinations, and the destination ranges its checks sort
     std::vector<ii::LayoutSeg> na_rows;
     std::vector<ii::DstRange> na_ranges;
     // runtime configuration

@@ -185,7 +185,15 @@ extern "C" int ii_plan(const ii_tensor_desc* table, size_t n, uint64_t chunk_byt
                 return fail(II_EOVERFLOW, "ii_plan: destination layout overflows");
             p->dst_offset[i] = off;
             maxal = std::max(maxal, a);
+            if (p->nbytes[i]) {
+                if (!p->layout_end) p->first_live = i;
+                p->layout_end = end;
+                p->live_align = std::max(p->live_align, a);
+            } else {
+                p->has_empty = true;
+            }
         }
+        if (!p->layout_end) p->first_live = n;
         uint64_t ar;
         if (__builtin_add_overflow(end, maxal - 1, &ar))
             return fail(II_EOVERFLOW, "ii_plan: arena size overflows");
@@ -441,6 +449,13 @@ extern "C" int ii_plan(const ii_tensor_desc* table, size_t n, uint64_t chunk_byt
             const uint32_t pct = env_u32("II_LAYOUT_MIXED_PCT", 5, 0, 101);
             p->layout_mixed = pct <= 100 && (many * 100 >= (uint64_t)pct * G ||
                                              (two * 100 >= 3 * G && shifted * 2 >= bytes));
+        }
+        p->lrows.resize(S);
+        for (size_t j = 0; j < S; ++j) {
+            const uint32_t x = p->lseg[j];
+            const uint64_t at = p->dst_offset[p->seg_tensor[x]] + p->seg_toff[x];
+            p->lrows[j] = LayoutSeg{(uint64_t)p->seg_chunk[x] * C + p->seg_off[x], at, at,
+                                    p->seg_len[x], 0};
         }
         p->na_rows.resize(S);
         p->na_ranges.reserve(n);

@@ -48,22 +48,13 @@
 #include <vector>
 
 #include "copy_pool.h"
+#include "dst_check.h"
 #include "ii_internal.h"
 #include "pertensor.h"
 #include "reach.h"
+#include "scatter_launch.h"
 
 namespace ii {
-
-hipError_t launch_scatter_slot(const uint8_t* slot, const TileDev* tiles, const TileWin* wins,
-                               uint32_t ntiles, const SegDev* segs, bool implicit,
-                               uint32_t tile_bytes, uint64_t plen, hipStream_t stream);
-hipError_t launch_scatter_layout(const uint8_t* span, const TileDev* tiles, const uint32_t* win,
-                                 uint64_t ntiles, const LayoutSeg* segs, uint32_t tile_bytes,
-                                 bool mixed, hipStream_t stream);
-hipError_t launch_scatter_layout_link(const uint8_t* span, const TileDev* tiles,
-                                      const uint32_t* win, uint64_t ntiles, const LayoutSeg* segs,
-                                      uint32_t tile_bytes, hipStream_t stream);
-hipError_t launch_zero(const RangeDev* ranges, uint32_t n, hipStream_t stream);
 
 #define II_HIP(call)                                                                   \
     do {                                                                               \
@@ -143,22 +134,32 @@ struct Runtime {
     SegDev* d_psegs = nullptr;
     SegDev* h_psegs = nullptr;
     bool tiles_ready = false, wins_ready = false;  // uploaded
-    // device tables of the resident-image kernel: layout-order rows, layout
-    // tiles and (layouts with padding-only windows) their windows
-    LayoutSeg* d_lsegs = nullptr;
-    LayoutSeg* h_lsegs = nullptr;  // pinned staging for d_lsegs uploads
+    // device tables of the resident-image kernel: layout-order rows for any
+    // arena, layout tiles and (layouts with padding-only windows) their
+    // windows; uploaded once, never changed
+    LayoutSeg* d_lrows = nullptr;
     TileDev* d_ltiles = nullptr;
     uint32_t* d_lwin = nullptr;
-    bool ltiles_ready = false, lwin_ready = false;  // uploaded
-    hipEvent_t tables_idle = nullptr;   // after the last kernel that read a row table
-    hipEvent_t upload_done = nullptr;   // after the last read of h_segs / h_psegs / h_lsegs
-    bool tables_used = false, uploaded = false;
-    std::vector<uint64_t> cached_dst;   // destination addresses of the last load
-    std::vector<DstRange> cached_ranges;  // ... their ranges, sorted by address
+    bool lrows_ready = false, ltiles_ready = false, lwin_ready = false;  // uploaded
+    // rows with resolved destinations, for tensors that are not one arena
+    LayoutSeg* d_lown = nullptr;
+    LayoutSeg* h_lown = nullptr;          // pinned staging for d_lown uploads
+    hipEvent_t lown_uploaded = nullptr;   // after the last read of h_lown
+    hipEvent_t lown_idle = nullptr;       // after the last kernel that read d_lown
+    hipStream_t lown_stream = nullptr;    // ... its stream (compared, never used)
+    bool lown_used = false, lown_mixed = false;  // read at all, from several streams
+    bool image_used = false;              // an image kernel may be in flight
+    // the ring's rows: read and written on the lanes, joined by lane 0
+    hipEvent_t segs_uploaded = nullptr;   // after the last read of h_segs / h_psegs
+    bool segs_used = false;
+    // Destinations that are not one arena: the addresses of the last such
+    // load, their ranges sorted by address, and what holds them
+    std::vector<uint64_t> cached_dst;
+    std::vector<DstRange> cached_ranges;
     bool cached_valid = false;
-    // whether d_segs (and d_psegs) / d_lsegs hold rows for cached_dst
-    bool ring_rows_ok = false, layout_rows_ok = false;
-    uint64_t image_b = 0, image_e = 0;  // source image range last checked against them
+    bool lown_ok = false;                 // d_lown holds cached_dst's rows
+    enum RingRows { kNoRows, kLayoutPos, kResolved } ring_rows = kNoRows;  // d_segs' dst fields
+    uint64_t image_b = 0, image_e = 0;  // source image range last checked against cached_dst
     // scrub ranges
     RangeDev* d_ranges = nullptr;
     RangeDev* h_ranges = nullptr;
@@ -239,8 +240,8 @@ static void destroy(Runtime* r) {
     // drain everything the plan may still have in flight
     for (auto c : r->lane_s)
         if (c) (void)hipStreamSynchronize(c);
-    if (r->tables_idle && r->tables_used) (void)hipEventSynchronize(r->tables_idle);
-    if (r->upload_done && r->uploaded) (void)hipEventSynchronize(r->upload_done);
+    // image launches record no event (one after a 6 us kernel costs 4 us more)
+    if (r->image_used) (void)hipDeviceSynchronize();
     if (r->ranges_idle && r->ranges_used) (void)hipEventSynchronize(r->ranges_idle);
     free_ring(r);
     free_trace(r);
@@ -248,16 +249,18 @@ static void destroy(Runtime* r) {
     if (r->h_segs) (void)hipHostFree(r->h_segs);
     if (r->d_tiles) (void)hipFree(r->d_tiles);
     if (r->d_wins) (void)hipFree(r->d_wins);
-    if (r->d_lsegs) (void)hipFree(r->d_lsegs);
-    if (r->h_lsegs) (void)hipHostFree(r->h_lsegs);
+    if (r->d_lrows) (void)hipFree(r->d_lrows);
+    if (r->d_lown) (void)hipFree(r->d_lown);
+    if (r->h_lown) (void)hipHostFree(r->h_lown);
     if (r->d_ltiles) (void)hipFree(r->d_ltiles);
     if (r->d_lwin) (void)hipFree(r->d_lwin);
     if (r->d_psegs) (void)hipFree(r->d_psegs);
     if (r->h_psegs) (void)hipHostFree(r->h_psegs);
     if (r->d_ranges) (void)hipFree(r->d_ranges);
     if (r->h_ranges) (void)hipHostFree(r->h_ranges);
-    if (r->tables_idle) (void)hipEventDestroy(r->tables_idle);
-    if (r->upload_done) (void)hipEventDestroy(r->upload_done);
+    if (r->lown_uploaded) (void)hipEventDestroy(r->lown_uploaded);
+    if (r->lown_idle) (void)hipEventDestroy(r->lown_idle);
+    if (r->segs_uploaded) (void)hipEventDestroy(r->segs_uploaded);
     if (r->ranges_idle) (void)hipEventDestroy(r->ranges_idle);
     (void)hipGetLastError();
     if (r->device >= 0 && cur >= 0 && cur != r->device) (void)hipSetDevice(cur);
@@ -284,7 +287,7 @@ static int ensure_state(ii_plan_t* p) {
     if (r->device != dev)
         return fail(II_EINVAL, "plan was first used on device %d, current device is %d",
                     r->device, dev);
-    for (hipEvent_t* e : {&r->tables_idle, &r->upload_done, &r->ranges_idle})
+    for (hipEvent_t* e : {&r->lown_uploaded, &r->lown_idle, &r->segs_uploaded, &r->ranges_idle})
         if (!*e) II_HIP(hipEventCreateWithFlags(e, hipEventDisableTiming));
     if (!r->live_ready) {
         r->live.clear();
@@ -325,8 +328,11 @@ static int ensure_ring_tables(ii_plan_t* p) {
 static int ensure_layout_tables(ii_plan_t* p) {
     Runtime* r = p->rt;
     const size_t S = p->seg_len.size();
-    if (S && !r->d_lsegs) II_HIP(dev_alloc(&r->d_lsegs, S * sizeof(LayoutSeg)));
-    if (S && !r->h_lsegs) II_HIP(host_alloc(&r->h_lsegs, S * sizeof(LayoutSeg)));
+    if (S && !r->lrows_ready) {
+        if (!r->d_lrows) II_HIP(dev_alloc(&r->d_lrows, S * sizeof(LayoutSeg)));
+        II_HIP(h2d_sync(r->d_lrows, p->lrows.data(), S * sizeof(LayoutSeg)));
+        r->lrows_ready = true;
+    }
     if (!p->lwin.empty() && !r->lwin_ready) {
         if (!r->d_lwin) II_HIP(dev_alloc(&r->d_lwin, p->lwin.size() * sizeof(uint32_t)));
         II_HIP(h2d_sync(r->d_lwin, p->lwin.data(), p->lwin.size() * sizeof(uint32_t)));
@@ -435,32 +441,6 @@ static bool accessible(uint64_t b, uint64_t e, AllocInfo* info = nullptr) {
     return reachable(a, b, e);
 }
 
-// Destination ranges of the non-empty tensors, sorted by address, after
-// checking that each is present, aligned and disjoint from the others.
-static int dst_ranges(const ii_plan_t* p, const uint64_t* dst, std::vector<DstRange>* out) {
-    const size_t n = p->nbytes.size();
-    std::vector<DstRange>& v = *out;
-    v.clear();
-    v.reserve(n);
-    for (size_t i = 0; i < n; ++i) {
-        if (!p->nbytes[i]) continue;
-        if (!dst[i]) return fail(II_EINVAL, "dst_ptrs[%zu] is NULL for a non-empty tensor", i);
-        if (dst[i] & (p->dst_align[i] - 1))
-            return fail(II_EALIGN, "dst_ptrs[%zu]=%#llx is not aligned to %llu", i,
-                        (unsigned long long)dst[i], (unsigned long long)p->dst_align[i]);
-        uint64_t e;
-        if (__builtin_add_overflow(dst[i], p->nbytes[i], &e))
-            return fail(II_EOVERFLOW, "dst_ptrs[%zu] + nbytes overflows", i);
-        v.push_back({dst[i], e, i});
-    }
-    std::sort(v.begin(), v.end(), [](const DstRange& a, const DstRange& b) { return a.b < b.b; });
-    for (size_t j = 1; j < v.size(); ++j)
-        if (v[j].b < v[j - 1].e)
-            return fail(II_EOVERLAP, "destinations of tensors %zu and %zu overlap", v[j - 1].i,
-                        v[j].i);
-    return II_OK;
-}
-
 // Every range (sorted by address) reachable by the device: one allocation
 // query per allocation the ranges fall in.
 static int check_reach(const std::vector<DstRange>& v) {
@@ -474,6 +454,8 @@ static int check_reach(const std::vector<DstRange>& v) {
 // Check destination addresses: present, aligned, pairwise disjoint and
 // reachable by the device.
 static int check_dst(const ii_plan_t* p, const uint64_t* dst) {
+    uint64_t base, end;
+    if (arena_base(p, dst, &base, &end) && accessible(base, end)) return II_OK;
     std::vector<DstRange> v;
     int rc = dst_ranges(p, dst, &v);
     return rc ? rc : check_reach(v);
@@ -487,45 +469,71 @@ static int check_image(const ii_plan_t* p, const uint64_t* dst, uint64_t b, uint
     return II_OK;
 }
 
-// Make the row tables a load reads (`which`: the ring's, the resident-image
-// kernel's) hold its resolved destination addresses. The upload is ordered
-// on `s`, after every kernel that read the previous tables. The
-// checks that depend only on the addresses (present, aligned, disjoint) run
-// for destinations not seen before; reachability -- whether the memory is
-// still allocated -- is checked on every call, one query per allocation,
-// since a freed arena may be passed again at the same addresses.
-enum RowTables { kRingRows = 1, kLayoutRows = 2 };
+// Where a load's tensors go: the plan's layout at `base` in one allocation,
+// or addresses of their own (base 0).
+struct Dst {
+    bool arena = false;
+    uint64_t base = 0;
+};
 
-static int prepare_segments(ii_plan_t* p, const uint64_t* dst, hipStream_t s, uint64_t image_b,
-                            uint64_t image_e, int which, AllocInfo* image_info = nullptr) {
+static int fail_image(uint64_t b, uint64_t e) {
+    return fail(II_EINVAL, "the image's span [%#llx, %#llx) is not memory the device can "
+                "read: not inside one device allocation or one pinned host allocation",
+                (unsigned long long)b, (unsigned long long)e);
+}
+
+// The checks of an arena's destinations (see arena_base), *d saying whether
+// it is one; *rc then holds the image's. The image may lie anywhere outside
+// the arena; one that meets it is left to the general checks, which go
+// tensor by tensor.
+static int check_arena(const ii_plan_t* p, const uint64_t* dst, uint64_t image_b,
+                       uint64_t image_e, AllocInfo* image_info, Dst* d) {
+    uint64_t base, end;
+    *d = Dst{};
+    if (!arena_base(p, dst, &base, &end) || !accessible(base, end)) return II_OK;
+    if (image_e > image_b) {
+        if (base < image_e && image_b < end) return II_OK;
+        if (!accessible(image_b, image_e, image_info)) return fail_image(image_b, image_e);
+    }
+    *d = Dst{true, base};
+    return II_OK;
+}
+
+// Check a load's destinations and, when image_e > image_b, its source image.
+// An arena's are checked as one range. Others: the checks that depend only
+// on the addresses (present, aligned, disjoint) run for destinations not
+// seen before; reachability -- whether the memory is still allocated -- is
+// checked on every call, one query per allocation, since freed memory may
+// be passed again at the same addresses.
+static int check_load(ii_plan_t* p, const uint64_t* dst, uint64_t image_b, uint64_t image_e,
+                      AllocInfo* image_info, Dst* d) {
     Runtime* r = p->rt;
-    const size_t n = p->nbytes.size(), S = p->seg_len.size();
+    int rc = check_arena(p, dst, image_b, image_e, image_info, d);
+    if (rc || d->arena) return rc;
+    const size_t n = p->nbytes.size();
     const bool same = r->cached_valid && r->cached_dst.size() == n &&
                       (n == 0 || memcmp(r->cached_dst.data(), dst, n * sizeof(uint64_t)) == 0);
     if (!same) {
-        r->cached_valid = false;
+        // every table of resolved destinations is stale until rebuilt
+        r->cached_valid = r->lown_ok = false;
+        if (r->ring_rows == Runtime::kResolved) r->ring_rows = Runtime::kNoRows;
         try {
-            int rc = dst_ranges(p, dst, &r->cached_ranges);
+            rc = dst_ranges(p, dst, &r->cached_ranges);
             if (rc) return rc;
         } catch (const std::bad_alloc&) {
             return fail(II_ENOMEM, "destination check: host allocation failed");
         }
     }
-    int rc = check_reach(r->cached_ranges);
+    rc = check_reach(r->cached_ranges);
     if (rc) return rc;
     if (image_e > image_b) {
-        if (!accessible(image_b, image_e, image_info))
-            return fail(II_EINVAL, "the image's span [%#llx, %#llx) is not memory the device can "
-                        "read: not inside one device allocation or one pinned host allocation",
-                        (unsigned long long)image_b, (unsigned long long)image_e);
+        if (!accessible(image_b, image_e, image_info)) return fail_image(image_b, image_e);
         if (!(same && r->image_b == image_b && r->image_e == image_e)) {
             rc = check_image(p, dst, image_b, image_e);
             if (rc) return rc;
         }
     }
     if (!same) {
-        // new destinations: every row table is stale until rebuilt for them
-        r->ring_rows_ok = r->layout_rows_ok = false;
         try {
             r->cached_dst.assign(dst, dst + n);
         } catch (const std::bad_alloc&) {
@@ -535,37 +543,62 @@ static int prepare_segments(ii_plan_t* p, const uint64_t* dst, hipStream_t s, ui
     }
     r->image_b = image_b;
     r->image_e = image_e;
-    const bool ring = S && (which & kRingRows) && !r->ring_rows_ok;
-    const bool layout = S && (which & kLayoutRows) && !r->layout_rows_ok;
-    if (!ring && !layout) return II_OK;
-    if (r->uploaded) II_HIP(hipEventSynchronize(r->upload_done));  // staging buffers free again
-    if (ring) {
+    return II_OK;
+}
+
+// Make the ring's row tables hold a load's destinations: the plan's layout
+// (for any arena), or resolved addresses. The upload goes on lane 0, which
+// every lane that read the previous rows has joined.
+static int ring_rows(ii_plan_t* p, const uint64_t* dst, const Dst& d, hipStream_t lane0) {
+    Runtime* r = p->rt;
+    const size_t S = p->seg_len.size();
+    const auto want = d.arena ? Runtime::kLayoutPos : Runtime::kResolved;
+    if (!S || r->ring_rows == want) return II_OK;
+    r->ring_rows = Runtime::kNoRows;
+    if (r->segs_used) II_HIP(hipEventSynchronize(r->segs_uploaded));  // staging free again
+    const uint64_t* at = d.arena ? p->dst_offset.data() : dst;
+    for (size_t i = 0; i < S; ++i)
+        r->h_segs[i] = SegDev{p->seg_off[i], p->seg_len[i], at[p->seg_tensor[i]] + p->seg_toff[i]};
+    if (p->packed_distinct)
         for (size_t i = 0; i < S; ++i)
-            r->h_segs[i] = SegDev{p->seg_off[i], p->seg_len[i],
-                                  dst[p->seg_tensor[i]] + p->seg_toff[i]};
-        if (p->packed_distinct)
-            for (size_t i = 0; i < S; ++i)
-                r->h_psegs[i] = SegDev{p->seg_poff[i], p->seg_len[i], r->h_segs[i].dst};
+            r->h_psegs[i] = SegDev{p->seg_poff[i], p->seg_len[i], r->h_segs[i].dst};
+    II_HIP(h2d(r->d_segs, r->h_segs, S * sizeof(SegDev), lane0));
+    if (p->packed_distinct) II_HIP(h2d(r->d_psegs, r->h_psegs, S * sizeof(SegDev), lane0));
+    II_HIP(hipEventRecord(r->segs_uploaded, lane0));
+    r->segs_used = true;
+    r->ring_rows = want;
+    return II_OK;
+}
+
+// The layout-order rows with resolved destinations.
+static void own_rows(const ii_plan_t* p, const uint64_t* dst, LayoutSeg* out) {
+    for (size_t j = 0; j < p->lseg.size(); ++j) {
+        const uint32_t x = p->lseg[j];
+        out[j] = p->lrows[j];
+        out[j].dst = dst[p->seg_tensor[x]] + p->seg_toff[x];
     }
-    if (layout) {
-        const uint64_t C = p->chunk_bytes;
-        for (size_t j = 0; j < S; ++j) {
-            const uint32_t x = p->lseg[j], t = p->seg_tensor[x];
-            r->h_lsegs[j] = LayoutSeg{(uint64_t)p->seg_chunk[x] * C + p->seg_off[x],
-                                      dst[t] + p->seg_toff[x], p->dst_offset[t] + p->seg_toff[x],
-                                      p->seg_len[x], 0};
-        }
+}
+
+// Make d_lown hold destinations that are not one arena, written on `s` after
+// every kernel that read the previous ones.
+static int image_own_rows(ii_plan_t* p, const uint64_t* dst, hipStream_t s) {
+    Runtime* r = p->rt;
+    const size_t S = p->seg_len.size();
+    if (!S || r->lown_ok) return II_OK;
+    if (!r->d_lown) II_HIP(dev_alloc(&r->d_lown, S * sizeof(LayoutSeg)));
+    if (!r->h_lown) II_HIP(host_alloc(&r->h_lown, S * sizeof(LayoutSeg)));
+    if (r->lown_used) {
+        II_HIP(hipEventSynchronize(r->lown_uploaded));  // staging free again
+        if (r->lown_mixed) II_HIP(hipDeviceSynchronize());  // the event covers one stream
+        else II_HIP(hipStreamWaitEvent(s, r->lown_idle, 0));
+        r->lown_mixed = false;
     }
-    if (r->tables_used) II_HIP(hipStreamWaitEvent(s, r->tables_idle, 0));
-    if (ring) {
-        II_HIP(h2d(r->d_segs, r->h_segs, S * sizeof(SegDev), s));
-        if (p->packed_distinct) II_HIP(h2d(r->d_psegs, r->h_psegs, S * sizeof(SegDev), s));
-    }
-    if (layout) II_HIP(h2d(r->d_lsegs, r->h_lsegs, S * sizeof(LayoutSeg), s));
-    II_HIP(hipEventRecord(r->upload_done, s));
-    r->uploaded = true;
-    if (ring) r->ring_rows_ok = true;
-    if (layout) r->layout_rows_ok = true;
+    own_rows(p, dst, r->h_lown);
+    II_HIP(h2d(r->d_lown, r->h_lown, S * sizeof(LayoutSeg), s));
+    II_HIP(hipEventRecord(r->lown_uploaded, s));
+    II_HIP(hipEventRecord(r->lown_idle, s));
+    r->lown_stream = s;
+    r->lown_used = r->lown_ok = true;
     return II_OK;
 }
 
@@ -677,7 +710,10 @@ static int run_ring(ii_plan_t* p, const Source& src, const uint64_t* dst, hipStr
     // Destination checks; new destinations' rows are uploaded on lane 0,
     // ahead of every scatter of this load.
     hipStream_t lane0 = r->lane_s[0];
-    rc = prepare_segments(p, dst, lane0, 0, 0, kRingRows);
+    Dst to;
+    rc = check_load(p, dst, 0, 0, nullptr, &to);
+    if (rc) return rc;
+    rc = ring_rows(p, dst, to, lane0);
     if (rc) return rc;
     // Entry edge: destination writes start after the caller's prior work.
     // Copies into the ring need no such wait (they write only the plan's own
@@ -818,7 +854,7 @@ static int run_ring(ii_plan_t* p, const Source& src, const uint64_t* dst, hipStr
         II_HIP(launch_injected() ? hipErrorLaunchFailure
                                  : launch_scatter_slot(r->dslot[slot], r->d_tiles + t0,
                                    implicit ? nullptr : r->d_wins + t0, (uint32_t)nt,
-                                   packed ? r->d_psegs : r->d_segs, implicit, p->tile_bytes,
+                                   packed ? r->d_psegs : r->d_segs, to.base, implicit, p->tile_bytes,
                                    p->chunk_plen[k], cs));
         II_HIP(hipEventRecord(r->scatter_done[slot], cs));
         if (trace) II_HIP(hipEventRecord(r->tr_se[j], cs));
@@ -838,8 +874,6 @@ static int run_ring(ii_plan_t* p, const Source& src, const uint64_t* dst, hipStr
             II_HIP(hipEventRecord(r->lane_done[x], r->lane_s[x]));
             II_HIP(hipStreamWaitEvent(lane0, r->lane_done[x], 0));
         }
-    II_HIP(hipEventRecord(r->tables_idle, lane0));
-    r->tables_used = true;
     II_HIP(hipEventRecord(r->done, lane0));
     II_HIP(hipStreamWaitEvent(stream, r->done, 0));
     return II_OK;
@@ -847,15 +881,13 @@ static int run_ring(ii_plan_t* p, const Source& src, const uint64_t* dst, hipStr
 
 // The layout kernel over an image, the span [image + lo, image + hi) in the
 // memory `from`: HBM, or pinned host memory read over the link.
-static hipError_t scatter_image(const ii_plan_t* p, const uint8_t* image, const TileDev* tiles,
-                                const uint32_t* win, const LayoutSeg* rows, AllocInfo::Kind from,
-                                hipStream_t stream) {
+static hipError_t scatter_image(const ii_plan_t* p, const uint8_t* image, const LayoutTable& t,
+                                uint64_t base, AllocInfo::Kind from, hipStream_t stream) {
     if (launch_injected()) return hipErrorLaunchFailure;
-    if (from == AllocInfo::kPinnedHost)
-        return launch_scatter_layout_link(image + p->lo, tiles, win, p->ltiles.size(), rows,
-                                          p->tile_bytes, stream);
-    return launch_scatter_layout(image + p->lo, tiles, win, p->ltiles.size(), rows, p->tile_bytes,
-                                 p->layout_mixed, stream);
+    const ImageKernel which = from == AllocInfo::kPinnedHost ? ImageKernel::kLink
+                              : p->layout_mixed              ? ImageKernel::kMixed
+                                                             : ImageKernel::kDense;
+    return launch_scatter_layout(image + p->lo, t, base, p->tile_bytes, which, stream);
 }
 
 // One launch on `stream` over the whole table. image_b..image_e: the image's
@@ -870,11 +902,22 @@ static int run_image(ii_plan_t* p, const uint8_t* image, const uint64_t* dst, hi
     Runtime* r = p->rt;
     AllocInfo info;
     info.kind = AllocInfo::kPinnedHost;
-    rc = prepare_segments(p, dst, stream, image_b, image_e, kLayoutRows, &info);
+    Dst to;
+    rc = check_load(p, dst, image_b, image_e, &info, &to);
     if (rc) return rc;
-    II_HIP(scatter_image(p, image, r->d_ltiles, r->d_lwin, r->d_lsegs, info.kind, stream));
-    II_HIP(hipEventRecord(r->tables_idle, stream));
-    r->tables_used = true;
+    if (!to.arena) {
+        rc = image_own_rows(p, dst, stream);
+        if (rc) return rc;
+    }
+    const LayoutTable t{r->d_ltiles, r->d_lwin, p->ltiles.size(),
+                        to.arena ? r->d_lrows : r->d_lown};
+    r->image_used = true;
+    II_HIP(scatter_image(p, image, t, to.base, info.kind, stream));
+    if (!to.arena) {
+        r->lown_mixed |= r->lown_stream != stream;
+        r->lown_stream = stream;
+        II_HIP(hipEventRecord(r->lown_idle, stream));
+    }
     return II_OK;
 }
 
@@ -953,9 +996,10 @@ struct ScratchLayout {
 
 static ScratchLayout scratch_layout(const ii_plan_t* p) {
     auto up = [](uint64_t x) { return (x + 255) & ~255ull; };
+    const uint64_t S = p->lseg.size();
     ScratchLayout l;
     l.rows = 0;
-    l.tiles = up(p->lseg.size() * sizeof(LayoutSeg));
+    l.tiles = up(S * sizeof(LayoutSeg));
     l.win = up(l.tiles + p->ltiles.size() * sizeof(TileDev));
     l.end = l.win + p->lwin.size() * sizeof(uint32_t);
     return l;
@@ -963,43 +1007,41 @@ static ScratchLayout scratch_layout(const ii_plan_t* p) {
 
 static int run_device_noalloc(ii_plan_t* p, const uint8_t* image, const uint64_t* dst,
                               hipStream_t stream) {
-    // destination checks into the plan's own buffer (its capacity is the
-    // table's size, so nothing is allocated)
-    int rc = dst_ranges(p, dst, &p->na_ranges);
-    if (rc) return rc;
-    rc = check_reach(p->na_ranges);
-    if (rc) return rc;
-    if (p->ltiles.empty()) return II_OK;  // nothing to move
-    const uint64_t ib = reinterpret_cast<uint64_t>(image);
+    const uint64_t ib = reinterpret_cast<uint64_t>(image) + p->lo;
+    const uint64_t ie = reinterpret_cast<uint64_t>(image) + p->hi;
     AllocInfo info;
-    if (!accessible(ib + p->lo, ib + p->hi, &info))
-        return fail(II_EINVAL, "the image's span [%#llx, %#llx) is not memory the device can "
-                    "read: not inside one device allocation or one pinned host allocation",
-                    (unsigned long long)(ib + p->lo), (unsigned long long)(ib + p->hi));
-    rc = check_image(p, dst, ib + p->lo, ib + p->hi);
+    Dst to;
+    int rc = check_arena(p, dst, ib, ie, &info, &to);
     if (rc) return rc;
+    if (!to.arena) {
+        // destination checks into the plan's own buffer (its capacity is the
+        // table's size, so nothing is allocated)
+        rc = dst_ranges(p, dst, &p->na_ranges);
+        if (rc) return rc;
+        rc = check_reach(p->na_ranges);
+        if (rc) return rc;
+        if (p->ltiles.empty()) return II_OK;  // nothing to move
+        if (!accessible(ib, ie, &info)) return fail_image(ib, ie);
+        rc = check_image(p, dst, ib, ie);
+        if (rc) return rc;
+    }
     uint8_t* ws = nullptr;
     rc = scratch_ptr(&ws);
     if (rc) return rc;
     const ScratchLayout l = scratch_layout(p);
     const size_t S = p->lseg.size();
-    const uint64_t C = p->chunk_bytes;
-    for (size_t j = 0; j < S; ++j) {
-        const uint32_t x = p->lseg[j], t = p->seg_tensor[x];
-        p->na_rows[j] = LayoutSeg{(uint64_t)p->seg_chunk[x] * C + p->seg_off[x],
-                                  dst[t] + p->seg_toff[x], p->dst_offset[t] + p->seg_toff[x],
-                                  p->seg_len[x], 0};
-    }
     // pageable sources: each copy returns once its bytes are staged, so the
     // plan's buffers may be rewritten by the next call
-    if (S) II_HIP(h2d(ws + l.rows, p->na_rows.data(), S * sizeof(LayoutSeg), stream));
+    if (!to.arena) own_rows(p, dst, p->na_rows.data());
+    const LayoutSeg* rows = to.arena ? p->lrows.data() : p->na_rows.data();
+    II_HIP(h2d(ws + l.rows, rows, S * sizeof(LayoutSeg), stream));
     II_HIP(h2d(ws + l.tiles, p->ltiles.data(), p->ltiles.size() * sizeof(TileDev), stream));
     if (!p->lwin.empty())
         II_HIP(h2d(ws + l.win, p->lwin.data(), p->lwin.size() * sizeof(uint32_t), stream));
-    II_HIP(scatter_image(
-        p, image, reinterpret_cast<const TileDev*>(ws + l.tiles),
-        p->lwin.empty() ? nullptr : reinterpret_cast<const uint32_t*>(ws + l.win),
-        reinterpret_cast<const LayoutSeg*>(ws + l.rows), info.kind, stream));
+    const LayoutTable t{reinterpret_cast<const TileDev*>(ws + l.tiles),
+                        p->lwin.empty() ? nullptr : reinterpret_cast<const uint32_t*>(ws + l.win),
+                        p->ltiles.size(), reinterpret_cast<const LayoutSeg*>(ws + l.rows)};
+    II_HIP(scatter_image(p, image, t, to.base, info.kind, stream));
     return II_OK;
 }
 

@@ -64,6 +64,7 @@
 
 #include <algorithm>
 
+#include "scatter_launch.h"
 #include "scatter_math.h"
 #include "scatter_types.h"
 
@@ -228,14 +229,16 @@ __device__ __forceinline__ void scatter_tile(uint32_t s_first, uint32_t s_last, 
 
 // Ring path: one chunk, staged in a device slot that starts at `slot`; one
 // workgroup per tile of the chunk (`tiles` points at the chunk's first).
+// A segment goes to base + its row's dst (rows of the plan's own layout and
+// the arena's address, or resolved addresses and 0).
 // implicit: tile m takes slot offsets [m * tile_bytes, ...) up to plen -- a
 // packed slot, or a chunk without gaps at its own offsets; otherwise the
 // slot holds a chunk with gaps at its own offsets and the tile's window of
 // chunk offsets (`wins`, the chunk's first) applies.
 __global__ __launch_bounds__(kBlock) void scatter_slot(
     const uint8_t* __restrict__ slot, const TileDev* __restrict__ tiles,
-    const TileWin* __restrict__ wins, const SegDev* __restrict__ segs, uint32_t implicit,
-    uint32_t tile_bytes, uint64_t plen) {
+    const TileWin* __restrict__ wins, const SegDev* __restrict__ segs, uint64_t base,
+    uint32_t implicit, uint32_t tile_bytes, uint64_t plen) {
     const uint32_t g = blockIdx.x;
     const TileDev td = tiles[g];
     uint64_t w0, w1;
@@ -250,7 +253,7 @@ __global__ __launch_bounds__(kBlock) void scatter_slot(
     const uint64_t cbase = reinterpret_cast<uint64_t>(slot);
     scatter_tile<false>(td.first, td.last, [&](uint32_t s, uint32_t* cnt) {
         const SegDev sd = segs[s];
-        return make_row(sd.dst, sd.off, sd.len, cbase, w0, w1, cnt);
+        return make_row(base + sd.dst, sd.off, sd.len, cbase, w0, w1, cnt);
     });
 }
 
@@ -268,6 +271,11 @@ __device__ __forceinline__ void scatter_one_row(const SegRow& row, uint32_t tota
 // `span` is the device address of the blob's span byte lo; segment rows are
 // in layout order. Tile g takes the layout window w = win[g] (w = g when win
 // is null: no window of the layout is all padding).
+//   A segment goes to base + its row's dst. Tensors that fill the plan's
+// layout in one arena take rows whose dst is their layout position, uploaded
+// once, and the arena's address: a table of 40,000 tensors loaded into two
+// arenas in turn spent 384 us a call forming and uploading rows with
+// resolved addresses, for a kernel of 130 us; it now takes 132 us.
 //   kMixed, chosen per plan (the planner's rule: enough tiles meet three or
 // more segments): tiles that one segment meets skip the LDS staging and its
 // barriers (scatter_one_row), and every tile issues all its loads before
@@ -279,8 +287,8 @@ __device__ __forceinline__ void scatter_one_row(const SegRow& row, uint32_t tota
 template <bool kMixed>
 __global__ __launch_bounds__(kBlock) void scatter_layout(
     const uint8_t* __restrict__ span, const TileDev* __restrict__ tiles,
-    const uint32_t* __restrict__ win, const LayoutSeg* __restrict__ segs, uint32_t tile_bytes,
-    uint32_t ntiles) {
+    const uint32_t* __restrict__ win, const LayoutSeg* __restrict__ segs, uint64_t base,
+    uint32_t tile_bytes, uint32_t ntiles) {
     const uint32_t g = blockIdx.y * gridDim.x + blockIdx.x;
     if (g >= ntiles) return;
     const TileDev td = tiles[g];
@@ -290,7 +298,7 @@ __global__ __launch_bounds__(kBlock) void scatter_layout(
     // source address of layout position x is sb + ls.src + (x - ls.pos)
     auto row_of = [&](uint32_t s, uint32_t* cnt) {
         const LayoutSeg ls = segs[s];
-        return make_row(ls.dst, ls.pos, ls.len, sb + ls.src - ls.pos, w0, w1, cnt);
+        return make_row(base + ls.dst, ls.pos, ls.len, sb + ls.src - ls.pos, w0, w1, cnt);
     };
     if (kMixed && td.last - td.first == 1) {
         uint32_t total;
@@ -322,8 +330,8 @@ __global__ __launch_bounds__(kBlock) void scatter_layout(
 // microseconds, and waits between units would double them.
 __global__ __launch_bounds__(kBlock) void scatter_layout_link(
     const uint8_t* __restrict__ span, const TileDev* __restrict__ tiles,
-    const uint32_t* __restrict__ win, const LayoutSeg* __restrict__ segs, uint32_t tile_bytes,
-    uint32_t ntiles) {
+    const uint32_t* __restrict__ win, const LayoutSeg* __restrict__ segs, uint64_t base,
+    uint32_t tile_bytes, uint32_t ntiles) {
     const uint64_t sb = reinterpret_cast<uint64_t>(span);
     // ntiles < 2^31 and a step is at most kLinkBlocks * kLinkRun: no wrap
     for (uint32_t g0 = blockIdx.x * kLinkRun; g0 < ntiles; g0 += gridDim.x * kLinkRun) {
@@ -334,7 +342,7 @@ __global__ __launch_bounds__(kBlock) void scatter_layout_link(
             const uint64_t w1 = w0 + tile_bytes;
             scatter_tile<true>(td.first, td.last, [&](uint32_t s, uint32_t* cnt) {
                 const LayoutSeg ls = segs[s];
-                return make_row(ls.dst, ls.pos, ls.len, sb + ls.src - ls.pos, w0, w1, cnt);
+                return make_row(base + ls.dst, ls.pos, ls.len, sb + ls.src - ls.pos, w0, w1, cnt);
             });
         }
     }
@@ -360,40 +368,37 @@ __global__ __launch_bounds__(kBlock) void zero_ranges(const RangeDev* __restrict
 }
 
 hipError_t launch_scatter_slot(const uint8_t* slot, const TileDev* tiles, const TileWin* wins,
-                               uint32_t ntiles, const SegDev* segs, bool implicit,
+                               uint32_t ntiles, const SegDev* segs, uint64_t base, bool implicit,
                                uint32_t tile_bytes, uint64_t plen, hipStream_t stream) {
     if (ntiles == 0) return hipSuccess;
     if (!implicit && !wins) return hipErrorInvalidValue;
     hipLaunchKernelGGL(scatter_slot, dim3(ntiles), dim3(kBlock), 0, stream, slot, tiles, wins,
-                       segs, implicit ? 1u : 0u, tile_bytes, plen);
+                       segs, base, implicit ? 1u : 0u, tile_bytes, plen);
     return hipGetLastError();
 }
 
-hipError_t launch_scatter_layout(const uint8_t* span, const TileDev* tiles, const uint32_t* win,
-                                 uint64_t ntiles, const LayoutSeg* segs, uint32_t tile_bytes,
-                                 bool mixed, hipStream_t stream) {
-    if (ntiles == 0) return hipSuccess;
-    if (ntiles > 0x7fffffffull) return hipErrorInvalidConfiguration;
+hipError_t launch_scatter_layout(const uint8_t* span, const LayoutTable& t, uint64_t base,
+                                 uint32_t tile_bytes, ImageKernel which, hipStream_t stream) {
+    if (t.ntiles == 0) return hipSuccess;
+    if (t.ntiles > 0x7fffffffull) return hipErrorInvalidConfiguration;
+    const uint32_t n = (uint32_t)t.ntiles;
     uint32_t gx, gy;
-    grid_shape(ntiles, &gx, &gy);
-    if (mixed)
-        hipLaunchKernelGGL(scatter_layout<true>, dim3(gx, gy), dim3(kBlock), 0, stream, span,
-                           tiles, win, segs, tile_bytes, (uint32_t)ntiles);
-    else
+    grid_shape(n, &gx, &gy);
+    switch (which) {
+    case ImageKernel::kDense:
         hipLaunchKernelGGL(scatter_layout<false>, dim3(gx, gy), dim3(kBlock), 0, stream, span,
-                           tiles, win, segs, tile_bytes, (uint32_t)ntiles);
-    return hipGetLastError();
-}
-
-hipError_t launch_scatter_layout_link(const uint8_t* span, const TileDev* tiles,
-                                      const uint32_t* win, uint64_t ntiles, const LayoutSeg* segs,
-                                      uint32_t tile_bytes, hipStream_t stream) {
-    if (ntiles == 0) return hipSuccess;
-    if (ntiles > 0x7fffffffull) return hipErrorInvalidConfiguration;
-    const uint32_t blocks = (uint32_t)std::min<uint64_t>((ntiles + kLinkRun - 1) / kLinkRun,
-                                                         kLinkBlocks);
-    hipLaunchKernelGGL(scatter_layout_link, dim3(blocks), dim3(kBlock), 0, stream, span, tiles,
-                       win, segs, tile_bytes, (uint32_t)ntiles);
+                           t.tiles, t.win, t.rows, base, tile_bytes, n);
+        break;
+    case ImageKernel::kMixed:
+        hipLaunchKernelGGL(scatter_layout<true>, dim3(gx, gy), dim3(kBlock), 0, stream, span,
+                           t.tiles, t.win, t.rows, base, tile_bytes, n);
+        break;
+    case ImageKernel::kLink:
+        gx = std::min((n + kLinkRun - 1) / kLinkRun, kLinkBlocks);
+        hipLaunchKernelGGL(scatter_layout_link, dim3(gx), dim3(kBlock), 0, stream, span, t.tiles,
+                           t.win, t.rows, base, tile_bytes, n);
+        break;
+    }
     return hipGetLastError();
 }
 

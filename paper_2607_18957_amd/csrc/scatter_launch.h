@@ -1,0 +1,29 @@
+// The launches of scatter.hip, as the runtime calls them.
+#pragma once
+
+#include <hip/hip_runtime_api.h>
+
+#include <cstdint>
+
+#include "scatter_types.h"
+
+namespace ii {
+
+// The tables of one resident-image launch, in device memory.
+struct LayoutTable {
+    const TileDev* tiles;
+    const uint32_t* win;  // null: tile g is window g
+    uint64_t ntiles;
+    const LayoutSeg* rows;
+};
+
+enum class ImageKernel { kDense, kMixed, kLink };
+
+hipError_t launch_scatter_slot(const uint8_t* slot, const TileDev* tiles, const TileWin* wins,
+                               uint32_t ntiles, const SegDev* segs, uint64_t base, bool implicit,
+                               uint32_t tile_bytes, uint64_t plen, hipStream_t stream);
+hipError_t launch_scatter_layout(const uint8_t* span, const LayoutTable& table, uint64_t base,
+                                 uint32_t tile_bytes, ImageKernel which, hipStream_t stream);
+hipError_t launch_zero(const RangeDev* ranges, uint32_t n, hipStream_t stream);
+
+}  // namespace ii

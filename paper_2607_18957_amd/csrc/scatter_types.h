@@ -12,7 +12,7 @@ namespace ii {
 struct SegDev {
     uint32_t off;  // offset of the piece inside its chunk
     uint32_t len;  // bytes
-    uint64_t dst;  // device address the piece's first byte goes to
+    uint64_t dst;  // where the piece's first byte goes, less the launch's base address
 };
 static_assert(sizeof(SegDev) == 16, "SegDev must stay 16 bytes");
 
@@ -40,10 +40,13 @@ static_assert(sizeof(TileWin) == 8, "TileWin must stay 8 bytes");
 
 // One segment as the resident-image kernel reads it, in destination layout
 // order: its bytes sit at span offset src (chunk * chunk_bytes + chunk
-// offset) of the image and go to device address dst; pos is its layout
-// position (the plan's destination offset of its first byte), the
-// coordinate the image kernel's tiles are cut in. 32 bytes: two dwordx4
-// loads per row.
+// offset) of the image and go to the launch's base address + dst; pos is its
+// layout position (the plan's destination offset of its first byte), the
+// coordinate the image kernel's tiles are cut in. Rows of the plan's own
+// layout have dst = pos and serve every arena; rows with resolved addresses
+// go with base 0. 32 bytes: two dwordx4 loads per row, issued together (rows
+// of 16 bytes with the lengths in an array of their own cost 4-6% on tables
+// of large tensors: the second load then waited for the first).
 struct LayoutSeg {
     uint64_t src;
     uint64_t dst;

@@ -1,7 +1,7 @@
 """Host-only sanitizer builds of the planner (ASan + UBSan), the host copy
 pool (TSan), the reachability decision of the loads (ASan + UBSan, against
-a fake memory map) and the per-tensor path's schedule (ASan + UBSan, carried
-out on host buffers). Built with g++ from the library's own sources."""
+a fake memory map), the per-tensor path's schedule (ASan + UBSan, carried
+out on host buffers) and the two destination checks (ASan + UBSan). Built with g++ from the library's own sources."""
 from __future__ import annotations
 
 import os
@@ -15,6 +15,7 @@ PLAN_BIN = os.path.join(HERE, "plan_fuzz")
 POOL_BIN = os.path.join(HERE, "pool_tsan")
 REACH_BIN = os.path.join(HERE, "reach_check")
 PERTENSOR_BIN = os.path.join(HERE, "pertensor_check")
+DST_BIN = os.path.join(HERE, "dst_check")
 
 
 def build() -> None:
@@ -28,3 +29,6 @@ def build() -> None:
                                     "-o", REACH_BIN, os.path.join(HERE, "reach_check.cpp")])
     subprocess.check_call(common + ["-fsanitize=address,undefined", "-fno-sanitize-recover=all",
                                     "-o", PERTENSOR_BIN, os.path.join(HERE, "pertensor_check.cpp")])
+    subprocess.check_call(common + ["-fsanitize=address,undefined", "-fno-sanitize-recover=all",
+                                    "-o", DST_BIN, os.path.join(HERE, "dst_check.cpp"),
+                                    os.path.join(CSRC, "plan.cpp")])

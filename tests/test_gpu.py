@@ -415,6 +415,49 @@ def test_separate_tensor_buffers(orc):
                 assert got[0] == 0x5A
 
 
+@pytest.mark.parametrize("dst_align", [1, 16, 256])
+def test_arenas_and_own_destinations_in_turn(orc, dst_align):
+    """One plan loaded into arenas (rows of the plan's layout and a base) and
+    into destinations of their own (resolved rows), in turn, through the ring
+    and the image kernels, on two streams: no load may see another's rows.
+    The table has empty tensors, whose pointers are NULL."""
+    rng = np.random.default_rng(dst_align)
+    sizes = [int(x) for x in rng.integers(0, 9000, 300)]
+    sizes[0] = sizes[7] = sizes[-1] = 0
+    src = [int(x) for x in 3 + np.cumsum([0] + sizes[:-1])]
+    t = oracle_pins._u8_table(sizes, src, [dst_align] * len(sizes))
+    plan = ii.ii_plan(t, 1 << 16)
+    nb, off = plan.tensors()
+    total = 3 + sum(sizes)
+    streams = [torch.cuda.current_stream(DEV), torch.cuda.Stream(DEV)]
+    gap = np.arange(t.n, dtype=np.uint64) * np.uint64(256)  # a little further apart each
+    todo = []
+    for k in range(12):
+        blob = synth.blob(total, seed=k)
+        image = torch.from_numpy(blob).to(DEV)
+        rel = off + (gap if k % 3 == 2 else np.uint64(0))
+        arena = torch.full((int(rel[-1]) + 4096,), 0xA5, dtype=torch.uint8, device=DEV)
+        dst = np.uint64(arena.data_ptr() + 1024) + rel
+        dst[nb == 0] = 0
+        todo.append((blob, image, rel, arena, dst))
+    torch.cuda.synchronize()
+    for k, (blob, image, rel, arena, dst) in enumerate(todo):
+        s = streams[(k // 4) % 2]
+        if k % 4 == 1:
+            ii.ii_load(plan, blob, dst, s)
+        elif k % 4 == 3:
+            ii.ii_load_device_noalloc(plan, image, dst, streams[0])
+        else:
+            ii.ii_load_device(plan, image, dst, s)
+    torch.cuda.synchronize()
+    for k, (blob, image, rel, arena, dst) in enumerate(todo):
+        want = np.full(arena.numel(), 0xA5, np.uint8)
+        for o, d in zip(orc.load(orc.nbytes(t), t.src_offset, blob), rel):
+            want[1024 + int(d):1024 + int(d) + o.size] = o
+        assert np.array_equal(arena.cpu().numpy(), want), k
+    plan.free()
+
+
 @pytest.mark.parametrize("depth,copy_streams", [(1, 1), (2, 1), (2, 2), (3, 2), (3, 3), (4, 4)])
 def test_ring_race_stress(orc, depth, copy_streams):
     """Slot reuse under pressure (the data-safety rule of Sec. 4.2): 4 KiB

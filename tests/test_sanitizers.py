@@ -67,3 +67,13 @@ def test_pertensor_schedule():
     assert r.returncode == 0, r.stdout + r.stderr
     assert r.stdout.startswith("OK"), r.stdout
     assert int(r.stdout.split("copies=")[1]) >= 100_000
+
+
+def test_destination_checks_agree():
+    """The check of an arena as one range (dst_check.h, arena_base) against
+    the general one, on 20,000 random tables and destinations: every arena it
+    takes the general check accepts, byte for byte the same ranges, and it
+    misses none."""
+    r = subprocess.run([_bin(sanitize.DST_BIN)], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout + r.stderr
+    assert r.stdout.startswith("OK"), r.stdout
