@@ -45,8 +45,11 @@ struct DstRange {
     size_t i;
 };
 
-// Static device workspace of ii_load_device_noalloc (runtime.hip).
+// Static device workspace of ii_load_device_noalloc (runtime.hip): the
+// kernel's tables, and after them what the segments' rows are formed from
+// (28 bytes for each 32-byte row).
 constexpr uint64_t kScratchBytes = 64ull << 20;
+constexpr uint64_t kStageBytes = kScratchBytes / 32 * 28;
 
 struct Runtime;  // device-side state (runtime.hip)
 
@@ -111,14 +114,17 @@ struct ii_plan_s {
     // lwin is empty: every window holds segment bytes) and the layout-order
     // segments [ltiles[g].first, ltiles[g].last) that meet it
     std::vector<uint32_t> lseg;
+    // their rows and lengths, from which the device forms the kernel's
+    std::vector<ii::LayoutRow> lrows;
+    std::vector<uint32_t> llen;
+    uint64_t nltiles = 0;
+    // kept only for layouts with padding-only windows; otherwise tile g is
+    // window g, and the ranges follow from the segments (row_tiles)
     std::vector<ii::TileDev> ltiles;
     std::vector<uint32_t> lwin;
     // whether the image kernel runs its variant for tables of many small
     // tensors (more loads in flight; see the planner's rule)
     bool layout_mixed = false;
-    // the segments in layout order as the image kernel reads them, for any
-    // arena (dst = pos)
-    std::vector<ii::LayoutSeg> lrows;
     // for the destination checks: the first non-empty tensor (n if none),
     // whether there are empty ones, the end of the last non-empty tensor in
     // the layout and the largest alignment of a non-empty one
@@ -126,9 +132,9 @@ struct ii_plan_s {
     bool has_empty = false;
     uint64_t layout_end = 0, live_align = 1;
     // host buffers of ii_load_device_noalloc, sized when the plan is made so
-    // that the call itself allocates nothing: the layout-order rows with
-    // resolved destinations, and the destination ranges its checks sort
-    std::vector<ii::LayoutSeg> na_rows;
+    // that the call itself allocates nothing: the layout-order segments'
+    // destinations, and the destination ranges its checks sort
+    std::vector<uint64_t> na_dst;
     std::vector<ii::DstRange> na_ranges;
     // runtime configuration
     uint32_t ring_depth = 3;

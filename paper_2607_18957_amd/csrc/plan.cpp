@@ -390,41 +390,71 @@ extern "C" int ii_plan(const ii_tensor_desc* table, size_t n, uint64_t chunk_byt
         // 7. layout tiles: the segments in destination layout order, cut into
         // windows of T layout positions. Layout positions grow with the table
         // order and, inside a tensor, with the tensor offset, so a table read
-        // in table order is already sorted. The windows a segment meets are
-        // visited in increasing order; a window gets a tile the first time a
-        // segment meets it, and later segments meeting it extend the tile's
-        // range. Windows holding only padding get no tile.
+        // in table order is already sorted. A window that holds segment bytes
+        // is a tile; windows holding only padding get none. Where every
+        // window is a tile, which segments meet which follows from the
+        // segments alone and the device works it out (row_tiles): only the
+        // tiles are counted here. Else ranges and windows are listed.
         {
+            p->lseg.resize(S);
+            for (size_t x = 0; x < S; ++x) p->lseg[x] = (uint32_t)x;
             std::vector<uint64_t> pos(S);
             for (size_t x = 0; x < S; ++x)
                 pos[x] = p->dst_offset[p->seg_tensor[x]] + p->seg_toff[x];
-            p->lseg.resize(S);
-            for (size_t x = 0; x < S; ++x) p->lseg[x] = (uint32_t)x;
             auto by_pos = [&pos](uint32_t a, uint32_t b) { return pos[a] < pos[b]; };
             if (!std::is_sorted(pos.begin(), pos.end()))
                 std::sort(p->lseg.begin(), p->lseg.end(), by_pos);
-            uint64_t cur = ~0ull;  // window of the last tile made
+            p->lrows.resize(S);
+            p->llen.resize(S);
+            p->na_dst.resize(S);
+            const uint32_t shift = tile_shift(T);
+            auto window = [&](uint64_t x) { return shift ? x >> shift : x / T; };
+            uint64_t cur = ~0ull;        // window of the last tile
+            uint64_t met = 0;            // segments meeting it so far
+            uint64_t G = 0, many = 0, two = 0, shifted = 0, bytes = 0;
+            bool gaps = false;           // a padding-only window lies before a tile
             for (size_t j = 0; j < S; ++j) {
                 const uint32_t x = p->lseg[j];
-                const uint64_t m0 = pos[x] / T, m1 = (pos[x] + p->seg_len[x] - 1) / T;
+                const uint64_t len = p->seg_len[x];
+                const uint64_t m0 = window(pos[x]), m1 = window(pos[x] + len - 1);
                 if (m1 >= (1ull << 32))
                     return fail(II_EINVAL, "ii_plan: destination layout beyond 2^32 tiles");
-                for (uint64_t m = m0; m <= m1; ++m) {
-                    if (m != cur) {
-                        if (p->ltiles.size() >= 0x7fffffffull)
-                            return fail(II_EINVAL, "ii_plan: more than 2^31 tiles");
-                        p->ltiles.push_back(TileDev{(uint32_t)j, (uint32_t)(j + 1)});
-                        p->lwin.push_back((uint32_t)m);
-                        cur = m;
-                    } else {
-                        p->ltiles.back().last = (uint32_t)(j + 1);
+                const uint64_t span_off = (uint64_t)p->seg_chunk[x] * C + p->seg_off[x];
+                p->lrows[j] = LayoutRow{span_off, pos[x]};
+                p->llen[j] = (uint32_t)len;
+                bytes += len;
+                if ((p->lo + span_off - pos[x]) & 15) shifted += len;
+                if (m0 != cur) {
+                    gaps |= m0 != cur + 1;
+                    ++G;
+                    met = 0;
+                }
+                ++met;
+                two += met == 2;
+                many += met == 3;
+                if (m1 > m0) {
+                    G += m1 - m0;
+                    met = 1;
+                }
+                cur = m1;
+                if (G > 0x7fffffffull) return fail(II_EINVAL, "ii_plan: more than 2^31 tiles");
+            }
+            p->nltiles = G;
+            if (gaps) {
+                p->ltiles.reserve(G);
+                p->lwin.reserve(G);
+                for (size_t j = 0; j < S; ++j) {
+                    const uint64_t m1 = window(p->lrows[j].pos + p->llen[j] - 1);
+                    for (uint64_t m = window(p->lrows[j].pos); m <= m1; ++m) {
+                        if (p->lwin.empty() || m != p->lwin.back()) {
+                            p->ltiles.push_back(TileDev{(uint32_t)j, (uint32_t)(j + 1)});
+                            p->lwin.push_back((uint32_t)m);
+                        } else {
+                            p->ltiles.back().last = (uint32_t)(j + 1);
+                        }
                     }
                 }
             }
-            // windows strictly increase from window 0 or more: every window
-            // holds segment bytes exactly when the last tile is window G - 1
-            if (p->ltiles.empty() || p->lwin.back() == p->ltiles.size() - 1)
-                std::vector<uint32_t>().swap(p->lwin);
             // The image kernel's variant for tables of many small tensors
             // (ii_plan_layout_mixed): when at least II_LAYOUT_MIXED_PCT
             // percent (default 5; 0 = always, 101 = never) of the tiles meet
@@ -435,29 +465,10 @@ extern "C" int ii_plan(const ii_tensor_desc* table, size_t n, uint64_t chunk_byt
             // more; 20,000 byte-sized tensors of 16-256 KiB, 4.3% of two and
             // shifted bytes; a tensor-parallel shard of 4-15 KB rows, aligned
             // rows; tables of large tensors, none of either.
-            uint64_t many = 0, two = 0, shifted = 0, bytes = 0;
-            for (const TileDev& td : p->ltiles) {
-                many += td.last - td.first >= 3;
-                two += td.last - td.first >= 2;
-            }
-            for (size_t x = 0; x < S; ++x) {
-                const uint64_t src = p->lo + (uint64_t)p->seg_chunk[x] * C + p->seg_off[x];
-                bytes += p->seg_len[x];
-                if ((src - pos[x]) & 15) shifted += p->seg_len[x];
-            }
-            const uint64_t G = p->ltiles.size();
             const uint32_t pct = env_u32("II_LAYOUT_MIXED_PCT", 5, 0, 101);
             p->layout_mixed = pct <= 100 && (many * 100 >= (uint64_t)pct * G ||
                                              (two * 100 >= 3 * G && shifted * 2 >= bytes));
         }
-        p->lrows.resize(S);
-        for (size_t j = 0; j < S; ++j) {
-            const uint32_t x = p->lseg[j];
-            const uint64_t at = p->dst_offset[p->seg_tensor[x]] + p->seg_toff[x];
-            p->lrows[j] = LayoutSeg{(uint64_t)p->seg_chunk[x] * C + p->seg_off[x], at, at,
-                                    p->seg_len[x], 0};
-        }
-        p->na_rows.resize(S);
         p->na_ranges.reserve(n);
     } catch (const std::bad_alloc&) {
         return fail(II_ENOMEM, "ii_plan: host allocation failed");
@@ -556,14 +567,29 @@ extern "C" int ii_plan_tiles(const ii_plan_t* p, uint32_t* tile_bytes, uint64_t*
 extern "C" int ii_plan_layout_tiles(const ii_plan_t* p, uint64_t* num_tiles, uint32_t* seg_order,
                                     uint32_t* first, uint32_t* last, uint32_t* window) {
     if (!p) return fail(II_EINVAL, "ii_plan_layout_tiles: plan is NULL");
-    const size_t G = p->ltiles.size(), S = p->lseg.size();
+    const size_t G = p->nltiles, S = p->lseg.size();
     if (num_tiles) *num_tiles = G;
     if (seg_order && S) memcpy(seg_order, p->lseg.data(), S * 4);
-    for (size_t g = 0; g < G; ++g) {
-        if (first) first[g] = p->ltiles[g].first;
-        if (last) last[g] = p->ltiles[g].last;
-        if (window) window[g] = p->lwin.empty() ? (uint32_t)g : p->lwin[g];
+    if (!p->lwin.empty()) {
+        for (size_t g = 0; g < G; ++g) {
+            if (first) first[g] = p->ltiles[g].first;
+            if (last) last[g] = p->ltiles[g].last;
+            if (window) window[g] = p->lwin[g];
+        }
+        return II_OK;
     }
+    // as the device forms them
+    const uint32_t shift = tile_shift(p->tile_bytes);
+    for (size_t j = 0; j < S && (first || last); ++j) {
+        const RowTiles t = row_tiles(p->lrows[j].pos, p->llen[j],
+                                     j ? p->lrows[j - 1].pos + p->llen[j - 1] : 0,
+                                     j + 1 < S ? p->lrows[j + 1].pos : ~0ull, p->tile_bytes, shift);
+        for (uint64_t m = t.m0; m <= t.m1; ++m) {
+            if (first && (m > t.m0 || t.first0)) first[m] = (uint32_t)j;
+            if (last && (m < t.m1 || t.last1)) last[m] = (uint32_t)(j + 1);
+        }
+    }
+    for (size_t g = 0; g < G && window; ++g) window[g] = (uint32_t)g;
     return II_OK;
 }
 

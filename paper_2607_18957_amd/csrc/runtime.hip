@@ -134,17 +134,16 @@ struct Runtime {
     SegDev* d_psegs = nullptr;
     SegDev* h_psegs = nullptr;
     bool tiles_ready = false, wins_ready = false;  // uploaded
-    // device tables of the resident-image kernel: layout-order rows for any
-    // arena, layout tiles and (layouts with padding-only windows) their
-    // windows; uploaded once, never changed
-    LayoutSeg* d_lrows = nullptr;
-    TileDev* d_ltiles = nullptr;
-    uint32_t* d_lwin = nullptr;
-    bool lrows_ready = false, ltiles_ready = false, lwin_ready = false;  // uploaded
-    // rows with resolved destinations, for tensors that are not one arena
+    // device tables of the resident-image kernel, one allocation, written
+    // once: what the segments' rows are formed from, their rows for any
+    // arena, layout tiles and (layouts with padding-only windows) windows
+    uint8_t* d_layout = nullptr;
+    bool layout_ready = false;
+    // rows with resolved destinations, for tensors that are not one arena,
+    // and the destinations they are formed from; one allocation
     LayoutSeg* d_lown = nullptr;
-    LayoutSeg* h_lown = nullptr;          // pinned staging for d_lown uploads
-    hipEvent_t lown_uploaded = nullptr;   // after the last read of h_lown
+    uint64_t* h_ldst = nullptr;           // pinned staging of the destinations
+    hipEvent_t lown_uploaded = nullptr;   // after the last read of h_ldst
     hipEvent_t lown_idle = nullptr;       // after the last kernel that read d_lown
     hipStream_t lown_stream = nullptr;    // ... its stream (compared, never used)
     bool lown_used = false, lown_mixed = false;  // read at all, from several streams
@@ -249,11 +248,9 @@ static void destroy(Runtime* r) {
     if (r->h_segs) (void)hipHostFree(r->h_segs);
     if (r->d_tiles) (void)hipFree(r->d_tiles);
     if (r->d_wins) (void)hipFree(r->d_wins);
-    if (r->d_lrows) (void)hipFree(r->d_lrows);
+    if (r->d_layout) (void)hipFree(r->d_layout);
     if (r->d_lown) (void)hipFree(r->d_lown);
-    if (r->h_lown) (void)hipHostFree(r->h_lown);
-    if (r->d_ltiles) (void)hipFree(r->d_ltiles);
-    if (r->d_lwin) (void)hipFree(r->d_lwin);
+    if (r->h_ldst) (void)hipHostFree(r->h_ldst);
     if (r->d_psegs) (void)hipFree(r->d_psegs);
     if (r->h_psegs) (void)hipHostFree(r->h_psegs);
     if (r->d_ranges) (void)hipFree(r->d_ranges);
@@ -325,24 +322,72 @@ static int ensure_ring_tables(ii_plan_t* p) {
     return II_OK;
 }
 
+// Where each of the image kernel's tables sits in a block of device memory
+// (offsets 256-aligned): rows, tiles and windows up to `end`, then what the
+// rows are formed from.
+struct LayoutBlock {
+    uint64_t rows, tiles, win, end, from, len, dst, all;
+};
+
+static LayoutBlock layout_block(const ii_plan_t* p) {
+    auto up = [](uint64_t x) { return (x + 255) & ~255ull; };
+    const uint64_t S = p->lseg.size();
+    LayoutBlock l;
+    l.rows = 0;
+    l.tiles = up(S * sizeof(LayoutSeg));
+    l.win = up(l.tiles + p->nltiles * sizeof(TileDev));
+    l.end = l.win + p->lwin.size() * sizeof(uint32_t);
+    l.from = up(l.end);
+    l.dst = l.from + S * sizeof(LayoutRow);
+    l.len = l.dst + S * sizeof(uint64_t);
+    l.all = l.len + S * sizeof(uint32_t);
+    return l;
+}
+
+static LayoutTable layout_table(const ii_plan_t* p, uint8_t* at, const LayoutBlock& l,
+                                const LayoutSeg* rows) {
+    return LayoutTable{reinterpret_cast<const TileDev*>(at + l.tiles),
+                       p->lwin.empty() ? nullptr : reinterpret_cast<const uint32_t*>(at + l.win),
+                       p->nltiles, rows};
+}
+
+// Upload and form a plan's tables in the block at `at`, ordered on `s`; dst:
+// the segments' destinations in layout order, or null for rows that serve
+// any arena. Pageable sources: each copy returns once its bytes are staged.
+static int put_layout(const ii_plan_t* p, uint8_t* at, const LayoutBlock& l, const uint64_t* dst,
+                      hipStream_t s) {
+    const size_t S = p->lseg.size();
+    if (!S) return II_OK;
+    const auto* from = reinterpret_cast<const LayoutRow*>(at + l.from);
+    const auto* len = reinterpret_cast<const uint32_t*>(at + l.len);
+    II_HIP(h2d(at + l.from, p->lrows.data(), S * sizeof(LayoutRow), s));
+    II_HIP(h2d(at + l.len, p->llen.data(), S * sizeof(uint32_t), s));
+    if (dst) II_HIP(h2d(at + l.dst, dst, S * sizeof(uint64_t), s));
+    const bool listed = !p->lwin.empty();
+    if (listed) {
+        II_HIP(h2d(at + l.tiles, p->ltiles.data(), p->ltiles.size() * sizeof(TileDev), s));
+        II_HIP(h2d(at + l.win, p->lwin.data(), p->lwin.size() * sizeof(uint32_t), s));
+    }
+    II_HIP(launch_injected()
+               ? hipErrorLaunchFailure
+               : launch_layout_tables(from, len,
+                                      dst ? reinterpret_cast<const uint64_t*>(at + l.dst) : nullptr,
+                                      (uint32_t)S, p->tile_bytes,
+                                      reinterpret_cast<LayoutSeg*>(at + l.rows),
+                                      listed ? nullptr : reinterpret_cast<TileDev*>(at + l.tiles),
+                                      s));
+    return II_OK;
+}
+
 static int ensure_layout_tables(ii_plan_t* p) {
     Runtime* r = p->rt;
-    const size_t S = p->seg_len.size();
-    if (S && !r->lrows_ready) {
-        if (!r->d_lrows) II_HIP(dev_alloc(&r->d_lrows, S * sizeof(LayoutSeg)));
-        II_HIP(h2d_sync(r->d_lrows, p->lrows.data(), S * sizeof(LayoutSeg)));
-        r->lrows_ready = true;
-    }
-    if (!p->lwin.empty() && !r->lwin_ready) {
-        if (!r->d_lwin) II_HIP(dev_alloc(&r->d_lwin, p->lwin.size() * sizeof(uint32_t)));
-        II_HIP(h2d_sync(r->d_lwin, p->lwin.data(), p->lwin.size() * sizeof(uint32_t)));
-        r->lwin_ready = true;
-    }
-    if (!p->ltiles.empty() && !r->ltiles_ready) {
-        if (!r->d_ltiles) II_HIP(dev_alloc(&r->d_ltiles, p->ltiles.size() * sizeof(TileDev)));
-        II_HIP(h2d_sync(r->d_ltiles, p->ltiles.data(), p->ltiles.size() * sizeof(TileDev)));
-        r->ltiles_ready = true;
-    }
+    if (r->layout_ready || p->lseg.empty()) return II_OK;
+    const LayoutBlock l = layout_block(p);
+    if (!r->d_layout) II_HIP(dev_alloc(&r->d_layout, l.all));
+    const int rc = put_layout(p, r->d_layout, l, nullptr, nullptr);
+    if (rc) return rc;
+    II_HIP(hipStreamSynchronize(nullptr));
+    r->layout_ready = true;
     return II_OK;
 }
 
@@ -570,12 +615,11 @@ static int ring_rows(ii_plan_t* p, const uint64_t* dst, const Dst& d, hipStream_
     return II_OK;
 }
 
-// The layout-order rows with resolved destinations.
-static void own_rows(const ii_plan_t* p, const uint64_t* dst, LayoutSeg* out) {
+// The destination of each layout-order segment.
+static void layout_dst(const ii_plan_t* p, const uint64_t* dst, uint64_t* out) {
     for (size_t j = 0; j < p->lseg.size(); ++j) {
         const uint32_t x = p->lseg[j];
-        out[j] = p->lrows[j];
-        out[j].dst = dst[p->seg_tensor[x]] + p->seg_toff[x];
+        out[j] = dst[p->seg_tensor[x]] + p->seg_toff[x];
     }
 }
 
@@ -585,17 +629,25 @@ static int image_own_rows(ii_plan_t* p, const uint64_t* dst, hipStream_t s) {
     Runtime* r = p->rt;
     const size_t S = p->seg_len.size();
     if (!S || r->lown_ok) return II_OK;
-    if (!r->d_lown) II_HIP(dev_alloc(&r->d_lown, S * sizeof(LayoutSeg)));
-    if (!r->h_lown) II_HIP(host_alloc(&r->h_lown, S * sizeof(LayoutSeg)));
+    if (!r->d_lown) II_HIP(dev_alloc(&r->d_lown, S * (sizeof(LayoutSeg) + sizeof(uint64_t))));
+    if (!r->h_ldst) II_HIP(host_alloc(&r->h_ldst, S * sizeof(uint64_t)));
     if (r->lown_used) {
         II_HIP(hipEventSynchronize(r->lown_uploaded));  // staging free again
         if (r->lown_mixed) II_HIP(hipDeviceSynchronize());  // the event covers one stream
         else II_HIP(hipStreamWaitEvent(s, r->lown_idle, 0));
         r->lown_mixed = false;
     }
-    own_rows(p, dst, r->h_lown);
-    II_HIP(h2d(r->d_lown, r->h_lown, S * sizeof(LayoutSeg), s));
+    layout_dst(p, dst, r->h_ldst);
+    uint64_t* const d_dst = reinterpret_cast<uint64_t*>(r->d_lown + S);
+    const LayoutBlock l = layout_block(p);
+    II_HIP(h2d(d_dst, r->h_ldst, S * sizeof(uint64_t), s));
     II_HIP(hipEventRecord(r->lown_uploaded, s));
+    r->lown_used = true;
+    II_HIP(launch_injected()
+               ? hipErrorLaunchFailure
+               : launch_layout_tables(reinterpret_cast<const LayoutRow*>(r->d_layout + l.from),
+                                      reinterpret_cast<const uint32_t*>(r->d_layout + l.len),
+                                      d_dst, (uint32_t)S, p->tile_bytes, r->d_lown, nullptr, s));
     II_HIP(hipEventRecord(r->lown_idle, s));
     r->lown_stream = s;
     r->lown_used = r->lown_ok = true;
@@ -905,12 +957,15 @@ static int run_image(ii_plan_t* p, const uint8_t* image, const uint64_t* dst, hi
     Dst to;
     rc = check_load(p, dst, image_b, image_e, &info, &to);
     if (rc) return rc;
+    if (p->lseg.empty()) return II_OK;  // nothing to move
     if (!to.arena) {
         rc = image_own_rows(p, dst, stream);
         if (rc) return rc;
     }
-    const LayoutTable t{r->d_ltiles, r->d_lwin, p->ltiles.size(),
-                        to.arena ? r->d_lrows : r->d_lown};
+    const LayoutBlock l = layout_block(p);
+    const LayoutTable t = layout_table(
+        p, r->d_layout, l,
+        to.arena ? reinterpret_cast<const LayoutSeg*>(r->d_layout + l.rows) : r->d_lown);
     r->image_used = true;
     II_HIP(scatter_image(p, image, t, to.base, info.kind, stream));
     if (!to.arena) {
@@ -960,7 +1015,7 @@ static int run_pinned(ii_plan_t* p, const uint8_t* blob, const uint64_t* dst, hi
 // `scratch`, a static device array each GPU holds for the life of the
 // process, uploaded on the call's stream every time (another plan's call may
 // have overwritten them in between).
-static __device__ __align__(256) uint8_t scratch[kScratchBytes];
+static __device__ __align__(256) uint8_t scratch[kScratchBytes + 256 + kStageBytes];
 
 constexpr int kMaxDevices = 64;
 static std::mutex g_scratch_mu;
@@ -989,22 +1044,6 @@ static int scratch_ptr(uint8_t** out) {
     return II_OK;
 }
 
-// Where each table of a plan sits in the workspace (offsets 256-aligned).
-struct ScratchLayout {
-    uint64_t rows, tiles, win, end;
-};
-
-static ScratchLayout scratch_layout(const ii_plan_t* p) {
-    auto up = [](uint64_t x) { return (x + 255) & ~255ull; };
-    const uint64_t S = p->lseg.size();
-    ScratchLayout l;
-    l.rows = 0;
-    l.tiles = up(S * sizeof(LayoutSeg));
-    l.win = up(l.tiles + p->ltiles.size() * sizeof(TileDev));
-    l.end = l.win + p->lwin.size() * sizeof(uint32_t);
-    return l;
-}
-
 static int run_device_noalloc(ii_plan_t* p, const uint8_t* image, const uint64_t* dst,
                               hipStream_t stream) {
     const uint64_t ib = reinterpret_cast<uint64_t>(image) + p->lo;
@@ -1020,7 +1059,7 @@ static int run_device_noalloc(ii_plan_t* p, const uint8_t* image, const uint64_t
         if (rc) return rc;
         rc = check_reach(p->na_ranges);
         if (rc) return rc;
-        if (p->ltiles.empty()) return II_OK;  // nothing to move
+        if (p->lseg.empty()) return II_OK;  // nothing to move
         if (!accessible(ib, ie, &info)) return fail_image(ib, ie);
         rc = check_image(p, dst, ib, ie);
         if (rc) return rc;
@@ -1028,19 +1067,11 @@ static int run_device_noalloc(ii_plan_t* p, const uint8_t* image, const uint64_t
     uint8_t* ws = nullptr;
     rc = scratch_ptr(&ws);
     if (rc) return rc;
-    const ScratchLayout l = scratch_layout(p);
-    const size_t S = p->lseg.size();
-    // pageable sources: each copy returns once its bytes are staged, so the
-    // plan's buffers may be rewritten by the next call
-    if (!to.arena) own_rows(p, dst, p->na_rows.data());
-    const LayoutSeg* rows = to.arena ? p->lrows.data() : p->na_rows.data();
-    II_HIP(h2d(ws + l.rows, rows, S * sizeof(LayoutSeg), stream));
-    II_HIP(h2d(ws + l.tiles, p->ltiles.data(), p->ltiles.size() * sizeof(TileDev), stream));
-    if (!p->lwin.empty())
-        II_HIP(h2d(ws + l.win, p->lwin.data(), p->lwin.size() * sizeof(uint32_t), stream));
-    const LayoutTable t{reinterpret_cast<const TileDev*>(ws + l.tiles),
-                        p->lwin.empty() ? nullptr : reinterpret_cast<const uint32_t*>(ws + l.win),
-                        p->ltiles.size(), reinterpret_cast<const LayoutSeg*>(ws + l.rows)};
+    const LayoutBlock l = layout_block(p);
+    if (!to.arena) layout_dst(p, dst, p->na_dst.data());
+    rc = put_layout(p, ws, l, to.arena ? nullptr : p->na_dst.data(), stream);
+    if (rc) return rc;
+    const LayoutTable t = layout_table(p, ws, l, reinterpret_cast<const LayoutSeg*>(ws + l.rows));
     II_HIP(scatter_image(p, image, t, to.base, info.kind, stream));
     return II_OK;
 }
@@ -1197,7 +1228,7 @@ extern "C" int ii_load_device(ii_plan_t* p, const void* dev_image, uint64_t imag
 extern "C" int ii_load_device_noalloc(ii_plan_t* p, const void* dev_image, uint64_t image_bytes,
                                       void* const* dst_ptrs, hipStream_t stream) {
     if (!p) return fail(II_EINVAL, "ii_load_device_noalloc: plan is NULL");
-    const ScratchLayout l = scratch_layout(p);
+    const LayoutBlock l = layout_block(p);
     if (l.end > kScratchBytes)
         return fail(II_ESCRATCH, "ii_load_device_noalloc: the plan's tables need %llu bytes, the "
                     "static workspace holds %llu", (unsigned long long)l.end,

@@ -348,6 +348,56 @@ __global__ __launch_bounds__(kBlock) void scatter_layout_link(
     }
 }
 
+// The image kernel's tables from what the host knows of each segment (20
+// bytes, 28 with a destination of its own): its 32-byte row, and its share
+// of the tiles' segment ranges, 8 bytes per 4 KiB of the layout. One thread
+// per segment writes its row and up to kFewTiles ranges; the ranges of a
+// longer segment are filled by its whole wavefront, shared between gridDim.y
+// workgroups.
+//   What it replaces is the host: building the ranges there and uploading
+// them was 31 MB for a Llama-8B-shaped table and most of a first load, and
+// ii_load_device_noalloc uploaded them on every call.
+constexpr uint32_t kTableBlock = 256;
+constexpr uint64_t kFewTiles = 8;
+
+__global__ __launch_bounds__(kTableBlock) void layout_tables(
+    const LayoutRow* __restrict__ from, const uint32_t* __restrict__ len,
+    const uint64_t* __restrict__ dst, uint32_t n, uint32_t tile_bytes, uint32_t shift,
+    LayoutSeg* __restrict__ rows, TileDev* __restrict__ tiles) {
+    const uint32_t j = blockIdx.x * kTableBlock + threadIdx.x;
+    RowTiles t{0, 0, false, false};
+    bool wide = false;
+    if (j < n) {
+        const LayoutRow r = from[j];
+        const uint32_t l = len[j];
+        const uint64_t prev_end = j ? from[j - 1].pos + len[j - 1] : 0;
+        const uint64_t next_pos = j + 1 < n ? from[j + 1].pos : ~0ull;
+        t = row_tiles(r.pos, l, prev_end, next_pos, tile_bytes, shift);
+        wide = t.m1 - t.m0 >= kFewTiles;
+        if (blockIdx.y == 0) rows[j] = LayoutSeg{r.src, dst ? dst[j] : r.pos, r.pos, l, 0};
+    }
+    if (!tiles) return;
+    auto put = [&](const RowTiles& rt, uint32_t s, uint64_t m) {
+        if (m > rt.m0 || rt.first0) tiles[m].first = s;
+        if (m < rt.m1 || rt.last1) tiles[m].last = s + 1;
+    };
+    if (j < n && !wide && blockIdx.y == 0)
+        for (uint64_t m = t.m0; m <= t.m1; ++m) put(t, j, m);
+    // every lane of the wavefront reaches this with its own t
+    const uint32_t lane = threadIdx.x & 63u;
+    for (uint64_t todo = __ballot(wide); todo; todo &= todo - 1) {
+        const int src = __ffsll((unsigned long long)todo) - 1;
+        RowTiles w;
+        w.m0 = __shfl(t.m0, src, 64);
+        w.m1 = __shfl(t.m1, src, 64);
+        w.first0 = __shfl((int)t.first0, src, 64) != 0;
+        w.last1 = __shfl((int)t.last1, src, 64) != 0;
+        const uint32_t s = j - lane + (uint32_t)src;
+        for (uint64_t m = w.m0 + blockIdx.y * 64u + lane; m <= w.m1; m += gridDim.y * 64u)
+            put(w, s, m);
+    }
+}
+
 // Zero the byte ranges [r.begin, r.end) (device addresses). One workgroup per
 // range; 16-byte stores for whole aligned blocks, exact narrow stores at the
 // edges.
@@ -399,6 +449,18 @@ hipError_t launch_scatter_layout(const uint8_t* span, const LayoutTable& t, uint
                            t.win, t.rows, base, tile_bytes, n);
         break;
     }
+    return hipGetLastError();
+}
+
+hipError_t launch_layout_tables(const LayoutRow* from, const uint32_t* len, const uint64_t* dst,
+                                uint32_t n, uint32_t tile_bytes, LayoutSeg* rows, TileDev* tiles,
+                                hipStream_t stream) {
+    if (n == 0) return hipSuccess;
+    const uint32_t gx = (uint32_t)(((uint64_t)n + kTableBlock - 1) / kTableBlock);
+    // long segments: enough workgroups in all to fill the chip
+    const uint32_t gy = tiles ? std::max(1u, std::min(256u, 1024u / gx)) : 1u;
+    hipLaunchKernelGGL(layout_tables, dim3(gx, gy), dim3(kTableBlock), 0, stream, from, len, dst,
+                       n, tile_bytes, tile_shift(tile_bytes), rows, tiles);
     return hipGetLastError();
 }
 

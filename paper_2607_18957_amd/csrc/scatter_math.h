@@ -37,6 +37,39 @@ II_HD void grid_shape(uint64_t n, uint32_t* gx, uint32_t* gy) {
     *gx = (uint32_t)(n ? (n + y - 1) / y : 1);
 }
 
+// The layout tiles one segment takes part in, for layouts whose windows all
+// hold segment bytes (tile m is window m): the segment meets tiles [m0, m1];
+// it is the first of tile m0 if the segment before it ends in an earlier
+// window, the last of tile m1 if the one after it starts in a later one, and
+// first and last of those between. So every tile's range is written whole by
+// exactly two of its segments (or twice by one), in any order.
+struct RowTiles {
+    uint64_t m0, m1;
+    bool first0, last1;
+};
+
+// log2(tile_bytes), or 0 if that is not a power of two (tile_bytes >= 1024)
+II_HD uint32_t tile_shift(uint32_t tile_bytes) {
+    if (tile_bytes & (tile_bytes - 1)) return 0;
+    uint32_t s = 0;
+    while ((tile_bytes >> s) > 1) ++s;
+    return s;
+}
+
+// A segment of len bytes at layout position pos; prev_end: where the segment
+// before it ends (0: none), next_pos: where the one after it starts (all
+// ones: none).
+II_HD RowTiles row_tiles(uint64_t pos, uint64_t len, uint64_t prev_end, uint64_t next_pos,
+                         uint32_t tile_bytes, uint32_t shift) {
+    auto window = [&](uint64_t x) { return shift ? x >> shift : x / tile_bytes; };
+    RowTiles t;
+    t.m0 = window(pos);
+    t.m1 = window(pos + len - 1);
+    t.first0 = !prev_end || window(prev_end - 1) < t.m0;
+    t.last1 = window(next_pos) > t.m1;
+    return t;
+}
+
 struct SegRow {
     uint64_t delta;  // source address minus destination address
     uint64_t dbeg;   // destination range [dbeg, dend)

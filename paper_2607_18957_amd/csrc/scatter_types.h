@@ -56,6 +56,15 @@ struct LayoutSeg {
 };
 static_assert(sizeof(LayoutSeg) == 32, "LayoutSeg must stay 32 bytes");
 
+// What a layout-order segment's LayoutSeg is formed from, on the device:
+// its source offset and layout position, with its length (u32) and, for
+// resolved rows, its destination (u64) in arrays of their own.
+struct LayoutRow {
+    uint64_t src;
+    uint64_t pos;
+};
+static_assert(sizeof(LayoutRow) == 16, "LayoutRow must stay 16 bytes");
+
 // Zero-fill range for the switch scrub: [begin, end) as device addresses.
 struct RangeDev {
     uint64_t begin;
