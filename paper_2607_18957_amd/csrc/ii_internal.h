@@ -114,9 +114,18 @@ struct ii_plan_s {
     // lwin is empty: every window holds segment bytes) and the layout-order
     // segments [ltiles[g].first, ltiles[g].last) that meet it
     std::vector<uint32_t> lseg;
-    // their rows and lengths, from which the device forms the kernel's
-    std::vector<ii::LayoutRow> lrows;
-    std::vector<uint32_t> llen;
+    // what the device forms the kernel's rows from, in the order it is
+    // uploaded in, so that one copy takes all: a destination per segment
+    // (written by ii_load_device_noalloc, which allocates nothing), a
+    // LayoutRow and a length
+    std::vector<uint64_t> lstage;
+    uint64_t* ldst() { return lstage.data(); }
+    const ii::LayoutRow* lrows() const {
+        return reinterpret_cast<const ii::LayoutRow*>(lstage.data() + lseg.size());
+    }
+    const uint32_t* llen() const {
+        return reinterpret_cast<const uint32_t*>(lstage.data() + 3 * lseg.size());
+    }
     uint64_t nltiles = 0;
     // kept only for layouts with padding-only windows; otherwise tile g is
     // window g, and the ranges follow from the segments (row_tiles)
@@ -131,10 +140,8 @@ struct ii_plan_s {
     size_t first_live = 0;
     bool has_empty = false;
     uint64_t layout_end = 0, live_align = 1;
-    // host buffers of ii_load_device_noalloc, sized when the plan is made so
-    // that the call itself allocates nothing: the layout-order segments'
-    // destinations, and the destination ranges its checks sort
-    std::vector<uint64_t> na_dst;
+    // the destination ranges ii_load_device_noalloc's checks sort, sized when
+    // the plan is made so that the call itself allocates nothing
     std::vector<ii::DstRange> na_ranges;
     // runtime configuration
     uint32_t ring_depth = 3;

@@ -404,9 +404,9 @@ extern "C" int ii_plan(const ii_tensor_desc* table, size_t n, uint64_t chunk_byt
             auto by_pos = [&pos](uint32_t a, uint32_t b) { return pos[a] < pos[b]; };
             if (!std::is_sorted(pos.begin(), pos.end()))
                 std::sort(p->lseg.begin(), p->lseg.end(), by_pos);
-            p->lrows.resize(S);
-            p->llen.resize(S);
-            p->na_dst.resize(S);
+            p->lstage.resize(3 * S + (S + 1) / 2);
+            auto* const lrows = reinterpret_cast<LayoutRow*>(p->lstage.data() + S);
+            auto* const llen = reinterpret_cast<uint32_t*>(p->lstage.data() + 3 * S);
             const uint32_t shift = tile_shift(T);
             auto window = [&](uint64_t x) { return shift ? x >> shift : x / T; };
             uint64_t cur = ~0ull;        // window of the last tile
@@ -420,8 +420,8 @@ extern "C" int ii_plan(const ii_tensor_desc* table, size_t n, uint64_t chunk_byt
                 if (m1 >= (1ull << 32))
                     return fail(II_EINVAL, "ii_plan: destination layout beyond 2^32 tiles");
                 const uint64_t span_off = (uint64_t)p->seg_chunk[x] * C + p->seg_off[x];
-                p->lrows[j] = LayoutRow{span_off, pos[x]};
-                p->llen[j] = (uint32_t)len;
+                lrows[j] = LayoutRow{span_off, pos[x]};
+                llen[j] = (uint32_t)len;
                 bytes += len;
                 if ((p->lo + span_off - pos[x]) & 15) shifted += len;
                 if (m0 != cur) {
@@ -444,8 +444,8 @@ extern "C" int ii_plan(const ii_tensor_desc* table, size_t n, uint64_t chunk_byt
                 p->ltiles.reserve(G);
                 p->lwin.reserve(G);
                 for (size_t j = 0; j < S; ++j) {
-                    const uint64_t m1 = window(p->lrows[j].pos + p->llen[j] - 1);
-                    for (uint64_t m = window(p->lrows[j].pos); m <= m1; ++m) {
+                    const uint64_t m1 = window(lrows[j].pos + llen[j] - 1);
+                    for (uint64_t m = window(lrows[j].pos); m <= m1; ++m) {
                         if (p->lwin.empty() || m != p->lwin.back()) {
                             p->ltiles.push_back(TileDev{(uint32_t)j, (uint32_t)(j + 1)});
                             p->lwin.push_back((uint32_t)m);
@@ -580,10 +580,12 @@ extern "C" int ii_plan_layout_tiles(const ii_plan_t* p, uint64_t* num_tiles, uin
     }
     // as the device forms them
     const uint32_t shift = tile_shift(p->tile_bytes);
+    const LayoutRow* rows = p->lrows();
+    const uint32_t* len = p->llen();
     for (size_t j = 0; j < S && (first || last); ++j) {
-        const RowTiles t = row_tiles(p->lrows[j].pos, p->llen[j],
-                                     j ? p->lrows[j - 1].pos + p->llen[j - 1] : 0,
-                                     j + 1 < S ? p->lrows[j + 1].pos : ~0ull, p->tile_bytes, shift);
+        const RowTiles t =
+            row_tiles(rows[j].pos, len[j], j ? rows[j - 1].pos + len[j - 1] : 0,
+                      j + 1 < S ? rows[j + 1].pos : ~0ull, p->tile_bytes, shift);
         for (uint64_t m = t.m0; m <= t.m1; ++m) {
             if (first && (m > t.m0 || t.first0)) first[m] = (uint32_t)j;
             if (last && (m < t.m1 || t.last1)) last[m] = (uint32_t)(j + 1);

@@ -140,10 +140,8 @@ struct Runtime {
     uint8_t* d_layout = nullptr;
     bool layout_ready = false;
     // rows with resolved destinations, for tensors that are not one arena,
-    // and the destinations they are formed from; one allocation
+    // and what they are formed from; one allocation
     LayoutSeg* d_lown = nullptr;
-    uint64_t* h_ldst = nullptr;           // pinned staging of the destinations
-    hipEvent_t lown_uploaded = nullptr;   // after the last read of h_ldst
     hipEvent_t lown_idle = nullptr;       // after the last kernel that read d_lown
     hipStream_t lown_stream = nullptr;    // ... its stream (compared, never used)
     bool lown_used = false, lown_mixed = false;  // read at all, from several streams
@@ -250,12 +248,10 @@ static void destroy(Runtime* r) {
     if (r->d_wins) (void)hipFree(r->d_wins);
     if (r->d_layout) (void)hipFree(r->d_layout);
     if (r->d_lown) (void)hipFree(r->d_lown);
-    if (r->h_ldst) (void)hipHostFree(r->h_ldst);
     if (r->d_psegs) (void)hipFree(r->d_psegs);
     if (r->h_psegs) (void)hipHostFree(r->h_psegs);
     if (r->d_ranges) (void)hipFree(r->d_ranges);
     if (r->h_ranges) (void)hipHostFree(r->h_ranges);
-    if (r->lown_uploaded) (void)hipEventDestroy(r->lown_uploaded);
     if (r->lown_idle) (void)hipEventDestroy(r->lown_idle);
     if (r->segs_uploaded) (void)hipEventDestroy(r->segs_uploaded);
     if (r->ranges_idle) (void)hipEventDestroy(r->ranges_idle);
@@ -284,7 +280,7 @@ static int ensure_state(ii_plan_t* p) {
     if (r->device != dev)
         return fail(II_EINVAL, "plan was first used on device %d, current device is %d",
                     r->device, dev);
-    for (hipEvent_t* e : {&r->lown_uploaded, &r->lown_idle, &r->segs_uploaded, &r->ranges_idle})
+    for (hipEvent_t* e : {&r->lown_idle, &r->segs_uploaded, &r->ranges_idle})
         if (!*e) II_HIP(hipEventCreateWithFlags(e, hipEventDisableTiming));
     if (!r->live_ready) {
         r->live.clear();
@@ -326,7 +322,7 @@ static int ensure_ring_tables(ii_plan_t* p) {
 // (offsets 256-aligned): rows, tiles and windows up to `end`, then what the
 // rows are formed from.
 struct LayoutBlock {
-    uint64_t rows, tiles, win, end, from, len, dst, all;
+    uint64_t rows, tiles, win, end, stage, all;
 };
 
 static LayoutBlock layout_block(const ii_plan_t* p) {
@@ -337,10 +333,8 @@ static LayoutBlock layout_block(const ii_plan_t* p) {
     l.tiles = up(S * sizeof(LayoutSeg));
     l.win = up(l.tiles + p->nltiles * sizeof(TileDev));
     l.end = l.win + p->lwin.size() * sizeof(uint32_t);
-    l.from = up(l.end);
-    l.dst = l.from + S * sizeof(LayoutRow);
-    l.len = l.dst + S * sizeof(uint64_t);
-    l.all = l.len + S * sizeof(uint32_t);
+    l.stage = up(l.end);
+    l.all = l.stage + S * 28;
     return l;
 }
 
@@ -351,32 +345,48 @@ static LayoutTable layout_table(const ii_plan_t* p, uint8_t* at, const LayoutBlo
                        p->nltiles, rows};
 }
 
-// Upload and form a plan's tables in the block at `at`, ordered on `s`; dst:
-// the segments' destinations in layout order, or null for rows that serve
-// any arena. Pageable sources: each copy returns once its bytes are staged.
-static int put_layout(const ii_plan_t* p, uint8_t* at, const LayoutBlock& l, const uint64_t* dst,
+// Form a plan's rows (and, unless tiles is null, its tiles' ranges) on the
+// device, ordered on `s`; with own_dst the rows go to the destinations in
+// p->ldst(), else they serve any arena. What they are formed from goes as
+// arguments of the kernel where it fits and else into `stage` by one copy
+// (each copy crosses to a copy engine and back, ~19 us between two kernels);
+// of a pageable source, so it returns once its bytes are staged. For failure
+// injection rows and lengths are an upload each, whichever way they go.
+static int put_rows(const ii_plan_t* p, uint8_t* stage, LayoutSeg* rows, TileDev* tiles,
+                    bool own_dst, hipStream_t s) {
+    const uint32_t S = (uint32_t)p->lseg.size();
+    const uint64_t* words = p->lstage.data() + (own_dst ? 0 : S);
+    const uint64_t bytes = (own_dst ? 28ull : 20ull) * S;
+    II_HIP(injected(kSiteH2D) ? hipErrorUnknown : hipSuccess);
+    LayoutArgs args;
+    if (bytes <= sizeof args) {
+        II_HIP(injected(kSiteH2D) ? hipErrorUnknown : hipSuccess);
+        memcpy(args.words, words, bytes);
+        II_HIP(launch_injected() ? hipErrorLaunchFailure
+                                 : launch_layout_tables_by_value(args, own_dst, S, p->tile_bytes,
+                                                                 rows, tiles, s));
+        return II_OK;
+    }
+    II_HIP(h2d(stage, words, bytes, s));
+    const uint64_t* dst = own_dst ? reinterpret_cast<const uint64_t*>(stage) : nullptr;
+    const auto* from = reinterpret_cast<const LayoutRow*>(stage + (own_dst ? 8ull * S : 0));
+    II_HIP(launch_injected()
+               ? hipErrorLaunchFailure
+               : launch_layout_tables(from, reinterpret_cast<const uint32_t*>(from + S), dst, S,
+                                      p->tile_bytes, rows, tiles, p->nltiles, s));
+    return II_OK;
+}
+
+// Upload and form all of a plan's tables in the block at `at`.
+static int put_layout(const ii_plan_t* p, uint8_t* at, const LayoutBlock& l, bool own_dst,
                       hipStream_t s) {
-    const size_t S = p->lseg.size();
-    if (!S) return II_OK;
-    const auto* from = reinterpret_cast<const LayoutRow*>(at + l.from);
-    const auto* len = reinterpret_cast<const uint32_t*>(at + l.len);
-    II_HIP(h2d(at + l.from, p->lrows.data(), S * sizeof(LayoutRow), s));
-    II_HIP(h2d(at + l.len, p->llen.data(), S * sizeof(uint32_t), s));
-    if (dst) II_HIP(h2d(at + l.dst, dst, S * sizeof(uint64_t), s));
     const bool listed = !p->lwin.empty();
     if (listed) {
         II_HIP(h2d(at + l.tiles, p->ltiles.data(), p->ltiles.size() * sizeof(TileDev), s));
         II_HIP(h2d(at + l.win, p->lwin.data(), p->lwin.size() * sizeof(uint32_t), s));
     }
-    II_HIP(launch_injected()
-               ? hipErrorLaunchFailure
-               : launch_layout_tables(from, len,
-                                      dst ? reinterpret_cast<const uint64_t*>(at + l.dst) : nullptr,
-                                      (uint32_t)S, p->tile_bytes,
-                                      reinterpret_cast<LayoutSeg*>(at + l.rows),
-                                      listed ? nullptr : reinterpret_cast<TileDev*>(at + l.tiles),
-                                      s));
-    return II_OK;
+    return put_rows(p, at + l.stage, reinterpret_cast<LayoutSeg*>(at + l.rows),
+                    listed ? nullptr : reinterpret_cast<TileDev*>(at + l.tiles), own_dst, s);
 }
 
 static int ensure_layout_tables(ii_plan_t* p) {
@@ -384,7 +394,7 @@ static int ensure_layout_tables(ii_plan_t* p) {
     if (r->layout_ready || p->lseg.empty()) return II_OK;
     const LayoutBlock l = layout_block(p);
     if (!r->d_layout) II_HIP(dev_alloc(&r->d_layout, l.all));
-    const int rc = put_layout(p, r->d_layout, l, nullptr, nullptr);
+    const int rc = put_layout(p, r->d_layout, l, false, nullptr);
     if (rc) return rc;
     II_HIP(hipStreamSynchronize(nullptr));
     r->layout_ready = true;
@@ -629,25 +639,16 @@ static int image_own_rows(ii_plan_t* p, const uint64_t* dst, hipStream_t s) {
     Runtime* r = p->rt;
     const size_t S = p->seg_len.size();
     if (!S || r->lown_ok) return II_OK;
-    if (!r->d_lown) II_HIP(dev_alloc(&r->d_lown, S * (sizeof(LayoutSeg) + sizeof(uint64_t))));
-    if (!r->h_ldst) II_HIP(host_alloc(&r->h_ldst, S * sizeof(uint64_t)));
+    if (!r->d_lown) II_HIP(dev_alloc(&r->d_lown, S * (sizeof(LayoutSeg) + 28)));
     if (r->lown_used) {
-        II_HIP(hipEventSynchronize(r->lown_uploaded));  // staging free again
         if (r->lown_mixed) II_HIP(hipDeviceSynchronize());  // the event covers one stream
         else II_HIP(hipStreamWaitEvent(s, r->lown_idle, 0));
         r->lown_mixed = false;
     }
-    layout_dst(p, dst, r->h_ldst);
-    uint64_t* const d_dst = reinterpret_cast<uint64_t*>(r->d_lown + S);
-    const LayoutBlock l = layout_block(p);
-    II_HIP(h2d(d_dst, r->h_ldst, S * sizeof(uint64_t), s));
-    II_HIP(hipEventRecord(r->lown_uploaded, s));
-    r->lown_used = true;
-    II_HIP(launch_injected()
-               ? hipErrorLaunchFailure
-               : launch_layout_tables(reinterpret_cast<const LayoutRow*>(r->d_layout + l.from),
-                                      reinterpret_cast<const uint32_t*>(r->d_layout + l.len),
-                                      d_dst, (uint32_t)S, p->tile_bytes, r->d_lown, nullptr, s));
+    layout_dst(p, dst, p->ldst());
+    const int rc = put_rows(p, reinterpret_cast<uint8_t*>(r->d_lown + S), r->d_lown, nullptr, true,
+                            s);
+    if (rc) return rc;
     II_HIP(hipEventRecord(r->lown_idle, s));
     r->lown_stream = s;
     r->lown_used = r->lown_ok = true;
@@ -1068,8 +1069,8 @@ static int run_device_noalloc(ii_plan_t* p, const uint8_t* image, const uint64_t
     rc = scratch_ptr(&ws);
     if (rc) return rc;
     const LayoutBlock l = layout_block(p);
-    if (!to.arena) layout_dst(p, dst, p->na_dst.data());
-    rc = put_layout(p, ws, l, to.arena ? nullptr : p->na_dst.data(), stream);
+    if (!to.arena) layout_dst(p, dst, p->ldst());
+    rc = put_layout(p, ws, l, !to.arena, stream);
     if (rc) return rc;
     const LayoutTable t = layout_table(p, ws, l, reinterpret_cast<const LayoutSeg*>(ws + l.rows));
     II_HIP(scatter_image(p, image, t, to.base, info.kind, stream));

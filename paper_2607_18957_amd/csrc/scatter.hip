@@ -350,41 +350,57 @@ __global__ __launch_bounds__(kBlock) void scatter_layout_link(
 
 // The image kernel's tables from what the host knows of each segment (20
 // bytes, 28 with a destination of its own): its 32-byte row, and its share
-// of the tiles' segment ranges, 8 bytes per 4 KiB of the layout. One thread
-// per segment writes its row and up to kFewTiles ranges; the ranges of a
-// longer segment are filled by its whole wavefront, shared between gridDim.y
-// workgroups.
+// of the tiles' segment ranges, 8 bytes per 4 KiB of the layout.
 //   What it replaces is the host: building the ranges there and uploading
 // them was 31 MB for a Llama-8B-shaped table and most of a first load, and
 // ii_load_device_noalloc uploaded them on every call.
+//   kWave: one wavefront per segment fills its ranges, shared between
+// gridDim.y of them; without, one thread per segment, and only segments of
+// more than kFewTiles tiles are filled by their whole wavefront. A segment
+// of a few tiles keeps one lane of a wavefront busy, one of many needs them
+// all: 5,000 segments of 12 tiles on average take 4.6 us with a
+// wavefront each and 11 us with a thread each; 150,000 of 0.7 tiles take 5.8
+// us with a thread each.
 constexpr uint32_t kTableBlock = 256;
 constexpr uint64_t kFewTiles = 8;
 
-__global__ __launch_bounds__(kTableBlock) void layout_tables(
-    const LayoutRow* __restrict__ from, const uint32_t* __restrict__ len,
-    const uint64_t* __restrict__ dst, uint32_t n, uint32_t tile_bytes, uint32_t shift,
-    LayoutSeg* __restrict__ rows, TileDev* __restrict__ tiles) {
-    const uint32_t j = blockIdx.x * kTableBlock + threadIdx.x;
-    RowTiles t{0, 0, false, false};
-    bool wide = false;
+template <bool kWave>
+__device__ __forceinline__ void form_tables(const LayoutRow* __restrict__ from,
+                                            const uint32_t* __restrict__ len,
+                                            const uint64_t* __restrict__ dst, uint32_t n,
+                                            uint32_t tile_bytes, uint32_t shift,
+                                            LayoutSeg* __restrict__ rows,
+                                            TileDev* __restrict__ tiles) {
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t j = kWave ? blockIdx.x * (kTableBlock / 64) + (threadIdx.x >> 6)
+                             : blockIdx.x * kTableBlock + threadIdx.x;
+    RowTiles t{1, 0, false, false};  // no tiles
     if (j < n) {
         const LayoutRow r = from[j];
         const uint32_t l = len[j];
         const uint64_t prev_end = j ? from[j - 1].pos + len[j - 1] : 0;
         const uint64_t next_pos = j + 1 < n ? from[j + 1].pos : ~0ull;
         t = row_tiles(r.pos, l, prev_end, next_pos, tile_bytes, shift);
-        wide = t.m1 - t.m0 >= kFewTiles;
-        if (blockIdx.y == 0) rows[j] = LayoutSeg{r.src, dst ? dst[j] : r.pos, r.pos, l, 0};
+        if (blockIdx.y == 0 && (!kWave || lane == 0))
+            rows[j] = LayoutSeg{r.src, dst ? dst[j] : r.pos, r.pos, l, 0};
     }
     if (!tiles) return;
     auto put = [&](const RowTiles& rt, uint32_t s, uint64_t m) {
         if (m > rt.m0 || rt.first0) tiles[m].first = s;
         if (m < rt.m1 || rt.last1) tiles[m].last = s + 1;
     };
+    auto fill = [&](const RowTiles& rt, uint32_t s) {
+        for (uint64_t m = rt.m0 + blockIdx.y * 64u + lane; m <= rt.m1; m += gridDim.y * 64u)
+            put(rt, s, m);
+    };
+    if (kWave) {
+        if (j < n) fill(t, j);
+        return;
+    }
+    const bool wide = j < n && t.m1 - t.m0 >= kFewTiles;
     if (j < n && !wide && blockIdx.y == 0)
         for (uint64_t m = t.m0; m <= t.m1; ++m) put(t, j, m);
     // every lane of the wavefront reaches this with its own t
-    const uint32_t lane = threadIdx.x & 63u;
     for (uint64_t todo = __ballot(wide); todo; todo &= todo - 1) {
         const int src = __ffsll((unsigned long long)todo) - 1;
         RowTiles w;
@@ -392,10 +408,34 @@ __global__ __launch_bounds__(kTableBlock) void layout_tables(
         w.m1 = __shfl(t.m1, src, 64);
         w.first0 = __shfl((int)t.first0, src, 64) != 0;
         w.last1 = __shfl((int)t.last1, src, 64) != 0;
-        const uint32_t s = j - lane + (uint32_t)src;
-        for (uint64_t m = w.m0 + blockIdx.y * 64u + lane; m <= w.m1; m += gridDim.y * 64u)
-            put(w, s, m);
+        fill(w, j - lane + (uint32_t)src);
     }
+}
+
+template <bool kWave>
+__global__ __launch_bounds__(kTableBlock) void layout_tables(
+    const LayoutRow* __restrict__ from, const uint32_t* __restrict__ len,
+    const uint64_t* __restrict__ dst, uint32_t n, uint32_t tile_bytes, uint32_t shift,
+    LayoutSeg* __restrict__ rows, TileDev* __restrict__ tiles) {
+    form_tables<kWave>(from, len, dst, n, tile_bytes, shift, rows, tiles);
+}
+
+// The same with what the rows are formed from passed by value, in the order
+// destinations (if any), rows, lengths: a table of a small model needs no
+// upload (a copy from pageable memory takes the host 2.7 us for 512 bytes
+// and 4.4 us for 4 KiB, on top of the launch, and larger ones cross to a
+// copy engine and back, ~19 us of idle device each).
+__global__ __launch_bounds__(kTableBlock) void layout_tables_by_value(
+    LayoutArgs, uint32_t has_dst, uint32_t n, uint32_t tile_bytes, uint32_t shift,
+    LayoutSeg* __restrict__ rows, TileDev* __restrict__ tiles) {
+    // the first argument where it lies, at the start of the kernel's argument
+    // segment: indexed as a variable it would be copied to scratch, 3.5 KiB a
+    // lane (253 us)
+    const uint64_t* const words = (const uint64_t*)__builtin_amdgcn_kernarg_segment_ptr();
+    const uint64_t* const w = words + (has_dst ? n : 0);
+    form_tables<true>(reinterpret_cast<const LayoutRow*>(w),
+                      reinterpret_cast<const uint32_t*>(w + 2 * n),
+                      has_dst ? words : nullptr, n, tile_bytes, shift, rows, tiles);
 }
 
 // Zero the byte ranges [r.begin, r.end) (device addresses). One workgroup per
@@ -452,15 +492,40 @@ hipError_t launch_scatter_layout(const uint8_t* span, const LayoutTable& t, uint
     return hipGetLastError();
 }
 
+// Workgroups that share the ranges of long segments: enough in all to fill
+// the chip.
+static uint32_t table_slices(uint32_t gx, const TileDev* tiles) {
+    return tiles ? std::max(1u, std::min(256u, 1024u / gx)) : 1u;
+}
+
 hipError_t launch_layout_tables(const LayoutRow* from, const uint32_t* len, const uint64_t* dst,
                                 uint32_t n, uint32_t tile_bytes, LayoutSeg* rows, TileDev* tiles,
-                                hipStream_t stream) {
+                                uint64_t ntiles, hipStream_t stream) {
     if (n == 0) return hipSuccess;
-    const uint32_t gx = (uint32_t)(((uint64_t)n + kTableBlock - 1) / kTableBlock);
-    // long segments: enough workgroups in all to fill the chip
-    const uint32_t gy = tiles ? std::max(1u, std::min(256u, 1024u / gx)) : 1u;
-    hipLaunchKernelGGL(layout_tables, dim3(gx, gy), dim3(kTableBlock), 0, stream, from, len, dst,
-                       n, tile_bytes, tile_shift(tile_bytes), rows, tiles);
+    const uint32_t shift = tile_shift(tile_bytes);
+    if (tiles && ntiles >= 4ull * n) {
+        const uint32_t gx = (uint32_t)(((uint64_t)n + 3) / 4);
+        hipLaunchKernelGGL(layout_tables<true>, dim3(gx, table_slices(gx, tiles)),
+                           dim3(kTableBlock), 0, stream, from, len, dst, n, tile_bytes, shift,
+                           rows, tiles);
+    } else {
+        const uint32_t gx = (uint32_t)(((uint64_t)n + kTableBlock - 1) / kTableBlock);
+        hipLaunchKernelGGL(layout_tables<false>, dim3(gx, table_slices(gx, tiles)),
+                           dim3(kTableBlock), 0, stream, from, len, dst, n, tile_bytes, shift,
+                           rows, tiles);
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_layout_tables_by_value(const LayoutArgs& a, bool has_dst, uint32_t n,
+                                         uint32_t tile_bytes, LayoutSeg* rows, TileDev* tiles,
+                                         hipStream_t stream) {
+    if (n == 0) return hipSuccess;
+    if ((has_dst ? 28ull : 20ull) * n > sizeof a) return hipErrorInvalidValue;
+    const uint32_t gx = (n + 3) / 4;
+    hipLaunchKernelGGL(layout_tables_by_value, dim3(gx, table_slices(gx, tiles)),
+                       dim3(kTableBlock), 0, stream, a, has_dst ? 1u : 0u, n, tile_bytes,
+                       tile_shift(tile_bytes), rows, tiles);
     return hipGetLastError();
 }
 

@@ -28,7 +28,16 @@ hipError_t launch_scatter_layout(const uint8_t* span, const LayoutTable& table, 
 // and, unless tiles is null, the layout tiles' segment ranges.
 hipError_t launch_layout_tables(const LayoutRow* from, const uint32_t* len, const uint64_t* dst,
                                 uint32_t n, uint32_t tile_bytes, LayoutSeg* rows, TileDev* tiles,
-                                hipStream_t stream);
+                                uint64_t ntiles, hipStream_t stream);
+
+// The same for few segments, what the rows are formed from in the kernel's
+// arguments: n destinations if has_dst, n LayoutRows, n lengths.
+struct LayoutArgs {
+    uint64_t words[448];  // 3.5 KiB: 179 segments, 128 with destinations
+};
+hipError_t launch_layout_tables_by_value(const LayoutArgs& args, bool has_dst, uint32_t n,
+                                         uint32_t tile_bytes, LayoutSeg* rows, TileDev* tiles,
+                                         hipStream_t stream);
 hipError_t launch_zero(const RangeDev* ranges, uint32_t n, hipStream_t stream);
 
 }  // namespace ii
