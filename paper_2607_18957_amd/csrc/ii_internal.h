@@ -101,10 +101,10 @@ struct ii_plan_s {
     std::vector<uint64_t> chunk_run_begin;  // num_chunks + 1
     std::vector<uint32_t> run_off, run_poff, run_len;
     // ring tiles (see TileDev), chunk by chunk: what the scatter of one
-    // staged or in-place chunk runs over
+    // staged or in-place chunk runs over. Only their number is kept: which
+    // segments meet a tile, and its window, follow from the segments
+    // (ring_tiles, ring_window)
     uint32_t tile_bytes = ii::kDefaultTile;
-    std::vector<ii::TileDev> tiles;
-    std::vector<ii::TileWin> tile_win;       // plans with gaps only
     std::vector<uint64_t> chunk_tile_begin;  // num_chunks + 1
     // layout tiles (the resident-image kernel): the segments in destination
     // layout order -- lseg[j] is the j-th segment by layout position

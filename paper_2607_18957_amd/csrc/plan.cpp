@@ -346,46 +346,15 @@ extern "C" int ii_plan(const ii_tensor_desc* table, size_t n, uint64_t chunk_byt
         }
 
         // 6. ring tiles: per chunk, tile_bytes of segment bytes each (packed
-        // offsets), and -- for plans with gaps -- the same bytes as a window
-        // of chunk offsets. Built segment by segment: the tiles that start
-        // inside segment s begin their range at s, and every tile segment s
-        // reaches has s in its range, so whole runs of tiles are filled at
-        // once.
+        // offsets). Only counted; the device works out each tile's segments
+        // and, for plans with gaps, its window of chunk offsets.
         uint32_t T = env_u32("II_TILE_BYTES", kDefaultTile, 1024, kMaxTile) & ~15u;
         p->tile_bytes = T;
-        const std::vector<uint32_t>& po = p->seg_poff;
         p->chunk_tile_begin.assign(p->num_chunks + 1, 0);
         for (size_t k = 0; k < p->num_chunks; ++k)
             p->chunk_tile_begin[k + 1] = p->chunk_tile_begin[k] + (p->chunk_plen[k] + T - 1) / T;
-        const uint64_t G = p->chunk_tile_begin[p->num_chunks];
-        if (G > 0x7fffffffull) return fail(II_EINVAL, "ii_plan: more than 2^31 tiles");
-        p->tiles.resize(G);
-        if (p->packed_distinct) p->tile_win.resize(G);
-        for (size_t k = 0; k < p->num_chunks; ++k) {
-            const uint64_t s0 = p->chunk_seg_begin[k], s1 = p->chunk_seg_begin[k + 1];
-            const uint64_t g0 = p->chunk_tile_begin[k];
-            TileDev* td = p->tiles.data() + g0;
-            for (uint64_t x = s0; x < s1; ++x) {
-                const uint64_t P0 = po[x], P1 = P0 + p->seg_len[x];
-                const uint64_t m0 = P0 / T, m1 = (P1 - 1) / T;
-                // segment x is the first to meet tile m0 if it starts there
-                if (P0 == m0 * T) td[m0].first = (uint32_t)x;
-                td[m0].last = (uint32_t)(x + 1);
-                if (m1 > m0) std::fill(td + m0 + 1, td + m1 + 1, TileDev{(uint32_t)x, (uint32_t)(x + 1)});
-            }
-            if (!p->packed_distinct) continue;
-            // windows: tile m starts at the chunk offset of packed byte m*T,
-            // which lies in segment first[m]; it ends where tile m+1 starts,
-            // the chunk's last tile at its last segment's end
-            const uint64_t M = p->chunk_tile_begin[k + 1] - g0;
-            TileWin* tw = p->tile_win.data() + g0;
-            for (uint64_t m = 0; m < M; ++m) {
-                const uint32_t f = td[m].first;
-                tw[m].w0 = (uint32_t)(p->seg_off[f] + (m * T - po[f]));
-            }
-            for (uint64_t m = 0; m + 1 < M; ++m) tw[m].w1 = tw[m + 1].w0;
-            if (M) tw[M - 1].w1 = p->seg_off[s1 - 1] + p->seg_len[s1 - 1];
-        }
+        if (p->chunk_tile_begin[p->num_chunks] > 0x7fffffffull)
+            return fail(II_EINVAL, "ii_plan: more than 2^31 tiles");
 
         // 7. layout tiles: the segments in destination layout order, cut into
         // windows of T layout positions. Layout positions grow with the table
@@ -545,22 +514,30 @@ extern "C" int ii_plan_tiles(const ii_plan_t* p, uint32_t* tile_bytes, uint64_t*
                              uint32_t* w1) {
     if (!p) return fail(II_EINVAL, "ii_plan_tiles: plan is NULL");
     if (tile_bytes) *tile_bytes = p->tile_bytes;
-    if (num_tiles) *num_tiles = p->tiles.size();
-    // gap-free plans keep no windows or chunk indices: tile m of chunk k is
-    // the window [m * tile_bytes, ...) of the chunk
-    for (size_t k = 0; k < p->num_chunks; ++k)
-        for (uint64_t g = p->chunk_tile_begin[k]; g < p->chunk_tile_begin[k + 1]; ++g) {
-            if (chunk) chunk[g] = (uint32_t)k;
-            if (first) first[g] = p->tiles[g].first;
-            if (last) last[g] = p->tiles[g].last;
-            const uint64_t m = g - p->chunk_tile_begin[k];
-            const uint64_t b = m * p->tile_bytes;
-            if (w0) w0[g] = p->packed_distinct ? p->tile_win[g].w0 : (uint32_t)b;
-            if (w1)
-                w1[g] = p->packed_distinct ? p->tile_win[g].w1
-                                           : (uint32_t)std::min<uint64_t>(p->chunk_len(k),
-                                                                           b + p->tile_bytes);
+    if (num_tiles) *num_tiles = p->chunk_tile_begin[p->num_chunks];
+    if (!chunk && !first && !last && !w0 && !w1) return II_OK;
+    // as the device forms them (gap-free plans: tile m of chunk k is the
+    // window [m * tile_bytes, ...) of the chunk, which is the same)
+    const uint32_t T = p->tile_bytes, shift = tile_shift(T);
+    for (size_t k = 0; k < p->num_chunks; ++k) {
+        const uint64_t g0 = p->chunk_tile_begin[k], s1 = p->chunk_seg_begin[k + 1];
+        for (uint64_t x = p->chunk_seg_begin[k]; x < s1; ++x) {
+            const uint32_t off = p->seg_off[x], po = p->seg_poff[x], len = p->seg_len[x];
+            const bool ends = x + 1 == s1;
+            const RowTiles t = ring_tiles(po, len, ends, T, shift);
+            for (uint64_t m = t.m0; m <= t.m1; ++m) {
+                if (m > t.m0 || t.first0) {
+                    const uint32_t w = ring_window(off, po, m, T);
+                    if (chunk) chunk[g0 + m] = (uint32_t)k;
+                    if (first) first[g0 + m] = (uint32_t)x;
+                    if (w0) w0[g0 + m] = w;
+                    if (w1 && m) w1[g0 + m - 1] = w;
+                }
+                if (last && (m < t.m1 || t.last1)) last[g0 + m] = (uint32_t)(x + 1);
+            }
+            if (w1 && ends) w1[g0 + t.m1] = off + len;
         }
+    }
     return II_OK;
 }
 

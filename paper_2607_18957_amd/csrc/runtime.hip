@@ -117,9 +117,6 @@ static hipError_t h2d_2d(void* d, size_t dpitch, const void* s, size_t spitch, s
                               : hipMemcpy2DAsync(d, dpitch, s, spitch, w, h,
                                                  hipMemcpyHostToDevice, st);
 }
-static hipError_t h2d_sync(void* d, const void* s, size_t n) {
-    return injected(kSiteH2D) ? hipErrorUnknown : hipMemcpy(d, s, n, hipMemcpyHostToDevice);
-}
 static bool launch_injected() { return injected(kSiteLaunch); }
 
 struct Runtime {
@@ -133,7 +130,7 @@ struct Runtime {
     // segment rows with packed staging offsets (plans with packed_distinct)
     SegDev* d_psegs = nullptr;
     SegDev* h_psegs = nullptr;
-    bool tiles_ready = false, wins_ready = false;  // uploaded
+    bool tiles_ready = false;  // tiles and windows formed
     // device tables of the resident-image kernel, one allocation, written
     // once: what the segments' rows are formed from, their rows for any
     // arena, layout tiles and (layouts with padding-only windows) windows
@@ -294,8 +291,8 @@ static int ensure_state(ii_plan_t* p) {
 // Each table is allocated and uploaded separately, and counted as ready only
 // once its upload returned: a call that failed half-way (one allocation
 // made, the next refused) leaves nothing a later load would take for
-// initialised. The tile tables never change after they are uploaded
-// (synchronously, once per plan).
+// initialised. The tile tables never change after they are formed (waited
+// for, once per plan).
 static int ensure_ring_tables(ii_plan_t* p) {
     Runtime* r = p->rt;
     const size_t S = p->seg_len.size();
@@ -305,14 +302,21 @@ static int ensure_ring_tables(ii_plan_t* p) {
         if (!r->d_psegs) II_HIP(dev_alloc(&r->d_psegs, S * sizeof(SegDev)));
         if (!r->h_psegs) II_HIP(host_alloc(&r->h_psegs, S * sizeof(SegDev)));
     }
-    if (!p->tile_win.empty() && !r->wins_ready) {
-        if (!r->d_wins) II_HIP(dev_alloc(&r->d_wins, p->tile_win.size() * sizeof(TileWin)));
-        II_HIP(h2d_sync(r->d_wins, p->tile_win.data(), p->tile_win.size() * sizeof(TileWin)));
-        r->wins_ready = true;
-    }
-    if (!p->tiles.empty() && !r->tiles_ready) {
-        if (!r->d_tiles) II_HIP(dev_alloc(&r->d_tiles, p->tiles.size() * sizeof(TileDev)));
-        II_HIP(h2d_sync(r->d_tiles, p->tiles.data(), p->tiles.size() * sizeof(TileDev)));
+    if (S && !r->tiles_ready) {
+        const uint64_t G = p->chunk_tile_begin[p->num_chunks];
+        if (!r->d_tiles) II_HIP(dev_alloc(&r->d_tiles, G * sizeof(TileDev)));
+        if (p->packed_distinct && !r->d_wins) II_HIP(dev_alloc(&r->d_wins, G * sizeof(TileWin)));
+        // what they are formed from is staged where the rows go afterwards
+        auto* from = reinterpret_cast<RingSeg*>(r->h_segs);
+        for (size_t i = 0; i < S; ++i)
+            from[i] = RingSeg{p->seg_off[i], p->seg_poff[i], p->seg_len[i],
+                              (uint32_t)p->chunk_tile_begin[p->seg_chunk[i]]};
+        II_HIP(h2d(r->d_segs, from, S * sizeof(RingSeg), nullptr));
+        II_HIP(launch_injected()
+                   ? hipErrorLaunchFailure
+                   : launch_ring_tables(reinterpret_cast<const RingSeg*>(r->d_segs), (uint32_t)S,
+                                        p->tile_bytes, r->d_tiles, r->d_wins, G, nullptr));
+        II_HIP(hipStreamSynchronize(nullptr));
         r->tiles_ready = true;
     }
     return II_OK;

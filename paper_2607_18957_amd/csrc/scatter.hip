@@ -364,43 +364,23 @@ __global__ __launch_bounds__(kBlock) void scatter_layout_link(
 constexpr uint32_t kTableBlock = 256;
 constexpr uint64_t kFewTiles = 8;
 
-template <bool kWave>
-__device__ __forceinline__ void form_tables(const LayoutRow* __restrict__ from,
-                                            const uint32_t* __restrict__ len,
-                                            const uint64_t* __restrict__ dst, uint32_t n,
-                                            uint32_t tile_bytes, uint32_t shift,
-                                            LayoutSeg* __restrict__ rows,
-                                            TileDev* __restrict__ tiles) {
+// put(t, j, m) for each tile m of segment j's range t, by whichever lanes:
+// every lane of a wavefront calls this with its own segment (kWave: all with
+// the same).
+template <bool kWave, class Put>
+__device__ __forceinline__ void fill_tiles(const RowTiles& t, bool valid, uint32_t j, Put put) {
     const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t j = kWave ? blockIdx.x * (kTableBlock / 64) + (threadIdx.x >> 6)
-                             : blockIdx.x * kTableBlock + threadIdx.x;
-    RowTiles t{1, 0, false, false};  // no tiles
-    if (j < n) {
-        const LayoutRow r = from[j];
-        const uint32_t l = len[j];
-        const uint64_t prev_end = j ? from[j - 1].pos + len[j - 1] : 0;
-        const uint64_t next_pos = j + 1 < n ? from[j + 1].pos : ~0ull;
-        t = row_tiles(r.pos, l, prev_end, next_pos, tile_bytes, shift);
-        if (blockIdx.y == 0 && (!kWave || lane == 0))
-            rows[j] = LayoutSeg{r.src, dst ? dst[j] : r.pos, r.pos, l, 0};
-    }
-    if (!tiles) return;
-    auto put = [&](const RowTiles& rt, uint32_t s, uint64_t m) {
-        if (m > rt.m0 || rt.first0) tiles[m].first = s;
-        if (m < rt.m1 || rt.last1) tiles[m].last = s + 1;
-    };
     auto fill = [&](const RowTiles& rt, uint32_t s) {
         for (uint64_t m = rt.m0 + blockIdx.y * 64u + lane; m <= rt.m1; m += gridDim.y * 64u)
             put(rt, s, m);
     };
     if (kWave) {
-        if (j < n) fill(t, j);
+        if (valid) fill(t, j);
         return;
     }
-    const bool wide = j < n && t.m1 - t.m0 >= kFewTiles;
-    if (j < n && !wide && blockIdx.y == 0)
+    const bool wide = valid && t.m1 - t.m0 >= kFewTiles;
+    if (valid && !wide && blockIdx.y == 0)
         for (uint64_t m = t.m0; m <= t.m1; ++m) put(t, j, m);
-    // every lane of the wavefront reaches this with its own t
     for (uint64_t todo = __ballot(wide); todo; todo &= todo - 1) {
         const int src = __ffsll((unsigned long long)todo) - 1;
         RowTiles w;
@@ -412,6 +392,38 @@ __device__ __forceinline__ void form_tables(const LayoutRow* __restrict__ from,
     }
 }
 
+// The segment of a lane of the tables kernels.
+template <bool kWave>
+__device__ __forceinline__ uint32_t table_segment() {
+    return kWave ? blockIdx.x * (kTableBlock / 64) + (threadIdx.x >> 6)
+                 : blockIdx.x * kTableBlock + threadIdx.x;
+}
+
+template <bool kWave>
+__device__ __forceinline__ void form_tables(const LayoutRow* __restrict__ from,
+                                            const uint32_t* __restrict__ len,
+                                            const uint64_t* __restrict__ dst, uint32_t n,
+                                            uint32_t tile_bytes, uint32_t shift,
+                                            LayoutSeg* __restrict__ rows,
+                                            TileDev* __restrict__ tiles) {
+    const uint32_t j = table_segment<kWave>();
+    RowTiles t{1, 0, false, false};  // no tiles
+    if (j < n) {
+        const LayoutRow r = from[j];
+        const uint32_t l = len[j];
+        const uint64_t prev_end = j ? from[j - 1].pos + len[j - 1] : 0;
+        const uint64_t next_pos = j + 1 < n ? from[j + 1].pos : ~0ull;
+        t = row_tiles(r.pos, l, prev_end, next_pos, tile_bytes, shift);
+        if (blockIdx.y == 0 && (!kWave || (threadIdx.x & 63u) == 0))
+            rows[j] = LayoutSeg{r.src, dst ? dst[j] : r.pos, r.pos, l, 0};
+    }
+    if (!tiles) return;
+    fill_tiles<kWave>(t, j < n, j, [&](const RowTiles& rt, uint32_t s, uint64_t m) {
+        if (m > rt.m0 || rt.first0) tiles[m].first = s;
+        if (m < rt.m1 || rt.last1) tiles[m].last = s + 1;
+    });
+}
+
 template <bool kWave>
 __global__ __launch_bounds__(kTableBlock) void layout_tables(
     const LayoutRow* __restrict__ from, const uint32_t* __restrict__ len,
@@ -420,7 +432,39 @@ __global__ __launch_bounds__(kTableBlock) void layout_tables(
     form_tables<kWave>(from, len, dst, n, tile_bytes, shift, rows, tiles);
 }
 
-// The same with what the rows are formed from passed by value, in the order
+// The ring's tables the same way: a tile's segments, and for plans with gaps
+// its window of chunk offsets, which the segment it starts in knows, as it
+// knows the end of the window before. (Listed on the host and uploaded they
+// were 8 or 16 bytes per 4 KiB of the model: most of ii_plan, 17 ms for a
+// Llama-8B-shaped table, and 31 MB of the ring's set-up.)
+template <bool kWave>
+__global__ __launch_bounds__(kTableBlock) void ring_tables(const RingSeg* __restrict__ segs,
+                                                           uint32_t n, uint32_t tile_bytes,
+                                                           uint32_t shift,
+                                                           TileDev* __restrict__ tiles,
+                                                           TileWin* __restrict__ wins) {
+    const uint32_t j = table_segment<kWave>();
+    RowTiles t{1, 0, false, false};  // no tiles
+    if (j < n) {
+        const RingSeg r = segs[j];
+        const bool ends = j + 1 == n || segs[j + 1].tile0 != r.tile0;
+        t = ring_tiles(r.poff, r.len, ends, tile_bytes, shift);
+        if (wins && ends) wins[r.tile0 + t.m1].w1 = r.off + r.len;
+    }
+    fill_tiles<kWave>(t, j < n, j, [&](const RowTiles& rt, uint32_t s, uint64_t m) {
+        const RingSeg r = segs[s];
+        const uint64_t g = r.tile0 + m;
+        if (m < rt.m1 || rt.last1) tiles[g].last = s + 1;
+        if (!(m > rt.m0 || rt.first0)) return;
+        tiles[g].first = s;
+        if (!wins) return;
+        const uint32_t w = ring_window(r.off, r.poff, m, tile_bytes);
+        wins[g].w0 = w;
+        if (m) wins[g - 1].w1 = w;
+    });
+}
+
+// The layout tables with what the rows are formed from passed by value, in the order
 // destinations (if any), rows, lengths: a table of a small model needs no
 // upload (a copy from pageable memory takes the host 2.7 us for 512 bytes
 // and 4.4 us for 4 KiB, on top of the launch, and larger ones cross to a
@@ -513,6 +557,22 @@ hipError_t launch_layout_tables(const LayoutRow* from, const uint32_t* len, cons
         hipLaunchKernelGGL(layout_tables<false>, dim3(gx, table_slices(gx, tiles)),
                            dim3(kTableBlock), 0, stream, from, len, dst, n, tile_bytes, shift,
                            rows, tiles);
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_ring_tables(const RingSeg* segs, uint32_t n, uint32_t tile_bytes, TileDev* tiles,
+                              TileWin* wins, uint64_t ntiles, hipStream_t stream) {
+    if (n == 0) return hipSuccess;
+    const uint32_t shift = tile_shift(tile_bytes);
+    if (ntiles >= 4ull * n) {
+        const uint32_t gx = (uint32_t)(((uint64_t)n + 3) / 4);
+        hipLaunchKernelGGL(ring_tables<true>, dim3(gx, table_slices(gx, tiles)), dim3(kTableBlock),
+                           0, stream, segs, n, tile_bytes, shift, tiles, wins);
+    } else {
+        const uint32_t gx = (uint32_t)(((uint64_t)n + kTableBlock - 1) / kTableBlock);
+        hipLaunchKernelGGL(ring_tables<false>, dim3(gx, table_slices(gx, tiles)),
+                           dim3(kTableBlock), 0, stream, segs, n, tile_bytes, shift, tiles, wins);
     }
     return hipGetLastError();
 }

@@ -24,6 +24,11 @@ hipError_t launch_scatter_slot(const uint8_t* slot, const TileDev* tiles, const 
                                uint32_t tile_bytes, uint64_t plen, hipStream_t stream);
 hipError_t launch_scatter_layout(const uint8_t* span, const LayoutTable& table, uint64_t base,
                                  uint32_t tile_bytes, ImageKernel which, hipStream_t stream);
+// Form the ring's tiles and, unless wins is null, their windows of chunk
+// offsets, from n segments.
+hipError_t launch_ring_tables(const RingSeg* segs, uint32_t n, uint32_t tile_bytes, TileDev* tiles,
+                              TileWin* wins, uint64_t ntiles, hipStream_t stream);
+
 // Form the layout rows of n segments (dst null: rows of the plan's layout)
 // and, unless tiles is null, the layout tiles' segment ranges.
 hipError_t launch_layout_tables(const LayoutRow* from, const uint32_t* len, const uint64_t* dst,

@@ -70,6 +70,20 @@ II_HD RowTiles row_tiles(uint64_t pos, uint64_t len, uint64_t prev_end, uint64_t
     return t;
 }
 
+// The ring tiles of its chunk a segment takes part in: its packed bytes
+// [poff, poff + len), right behind the segment before it; `ends`: it is its
+// chunk's last.
+II_HD RowTiles ring_tiles(uint32_t poff, uint32_t len, bool ends, uint32_t tile_bytes,
+                          uint32_t shift) {
+    return row_tiles(poff, len, poff, ends ? ~0ull : (uint64_t)poff + len, tile_bytes, shift);
+}
+
+// The chunk offset where tile m starts, m * tile_bytes lying in the segment:
+// the start of tile m's window and the end of tile m - 1's.
+II_HD uint32_t ring_window(uint32_t off, uint32_t poff, uint64_t m, uint32_t tile_bytes) {
+    return off + (uint32_t)(m * tile_bytes - poff);
+}
+
 struct SegRow {
     uint64_t delta;  // source address minus destination address
     uint64_t dbeg;   // destination range [dbeg, dend)

@@ -56,6 +56,17 @@ struct LayoutSeg {
 };
 static_assert(sizeof(LayoutSeg) == 32, "LayoutSeg must stay 32 bytes");
 
+// What the ring's tiles and windows are formed from, on the device: a
+// segment's offset in its chunk and in the packed layout, its length, and
+// the index of its chunk's first tile.
+struct RingSeg {
+    uint32_t off;
+    uint32_t poff;
+    uint32_t len;
+    uint32_t tile0;
+};
+static_assert(sizeof(RingSeg) == sizeof(SegDev), "staged where the ring's rows go");
+
 // What a layout-order segment's LayoutSeg is formed from, on the device:
 // its source offset and layout position, with its length (u32) and, for
 // resolved rows, its destination (u64) in arrays of their own.
