@@ -941,9 +941,9 @@ static int run_ring(ii_plan_t* p, const Source& src, const uint64_t* dst, hipStr
 static hipError_t scatter_image(const ii_plan_t* p, const uint8_t* image, const LayoutTable& t,
                                 uint64_t base, AllocInfo::Kind from, hipStream_t stream) {
     if (launch_injected()) return hipErrorLaunchFailure;
-    const ImageKernel which = from == AllocInfo::kPinnedHost ? ImageKernel::kLink
-                              : p->layout_mixed              ? ImageKernel::kMixed
-                                                             : ImageKernel::kDense;
+    const ImageKernel which = from == AllocInfo::kPinnedHost        ? ImageKernel::kLink
+                              : p->layout_mixed || p->layout_cached ? ImageKernel::kMixed
+                                                                    : ImageKernel::kDense;
     return launch_scatter_layout(image + p->lo, t, base, p->tile_bytes, which, stream);
 }
 

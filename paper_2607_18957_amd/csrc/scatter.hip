@@ -277,7 +277,7 @@ __device__ __forceinline__ void scatter_one_row(const SegRow& row, uint32_t tota
 // arenas in turn spent 384 us a call forming and uploading rows with
 // resolved addresses, for a kernel of 130 us; it now takes 132 us.
 //   kMixed, chosen per plan (the planner's rule: enough tiles meet three or
-// more segments): tiles that one segment meets skip the LDS staging and its
+// more segments, or the load fits the memory-side cache): tiles that one segment meets skip the LDS staging and its
 // barriers (scatter_one_row), and every tile issues all its loads before
 // using any (move_units). Both put more loads in flight sooner, which pays
 // where tiles spend long forming rows and costs on tables of large tensors

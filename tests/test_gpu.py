@@ -940,6 +940,20 @@ def test_image_kernel_both_variants(orc, monkeypatch, pct):
         plan.free()
 
 
+@pytest.mark.parametrize("extra", [0, 1])
+def test_image_at_the_cache_sized_limit(orc, extra):
+    """Image loads of exactly 300 MiB and of one byte more, the two sides of
+    the size up to which every table runs the variant with more loads in
+    flight."""
+    t = oracle_pins._u8_table([(300 << 20) + extra - 5, 5], [7, 1], [1, 64])
+    t.name = f"300 MiB + {extra}"
+    t.chunk_bytes = 64 << 20
+    plan = ii.ii_plan(t)
+    assert plan.payload_bytes == (300 << 20) + extra and not plan.layout_mixed
+    _load_arena(orc, t, mode="image", blob=synth.blob(int(t.src_offset[0]) + (300 << 20) + extra,
+                                                      seed=3), plan=plan)
+
+
 @pytest.mark.slow
 def test_largest_chunk(orc):
     """chunk_bytes at its maximum, 2^32 - 16: chunk offsets and tile windows
