@@ -259,11 +259,16 @@ __global__ __launch_bounds__(kBlock) void scatter_slot(
 
 // A tile that one segment meets, without LDS or barriers: every lane forms
 // the row itself (its prefix is 0, so unit u is unit u of the row) -- the
-// arithmetic of scatter_tile with a single row.
+// arithmetic of scatter_tile with a single row. One unit's loads at a time:
+// such a tile is one unbroken stream, and issuing both units' loads first
+// lengthens the queues as it does in a table of large tensors (100,000
+// tensors 327.9 -> 322.0 us, 40,000 130.7 -> 128.9; tables of large tensors
+// of 37 to 168 MB level). Tiles of several segments spend longer forming
+// rows and keep all their loads in flight (one at a time: 326 us).
 __device__ __forceinline__ void scatter_one_row(const SegRow& row, uint32_t total) {
     DevMem mem;
     for (uint32_t base = 0; base < total; base += kBlock * kUnroll)
-        move_units<true>(mem, base, total, [&](uint32_t) { return row; });
+        move_units<false>(mem, base, total, [&](uint32_t) { return row; });
 }
 
 // Resident-image path: the whole table in one dispatch (a grid of gy rows of
@@ -277,13 +282,14 @@ __device__ __forceinline__ void scatter_one_row(const SegRow& row, uint32_t tota
 // arenas in turn spent 384 us a call forming and uploading rows with
 // resolved addresses, for a kernel of 130 us; it now takes 132 us.
 //   kMixed, chosen per plan (the planner's rule: enough tiles meet three or
-// more segments, or the load fits the memory-side cache): tiles that one segment meets skip the LDS staging and its
-// barriers (scatter_one_row), and every tile issues all its loads before
-// using any (move_units). Both put more loads in flight sooner, which pays
-// where tiles spend long forming rows and costs on tables of large tensors
-// (measured, 100,000-tensor set: 71.2% of HBM peak against 65.7%; a
-// Llama-8B set: 77.2% against 83.4%; its rank-1-of-4 shard, whose tiles
-// meet at most two segments: 76.2% against 80.0%).
+// more segments, or the load fits the memory-side cache): tiles that one
+// segment meets skip the LDS staging and its barriers (scatter_one_row), and
+// the others issue all their loads before using any (move_units). Both put
+// loads in flight sooner, which pays where tiles spend long forming rows and
+// costs on large tables of large tensors (measured, dense and mixed:
+// 100,000-tensor set 330.1 and 322.0 us; a Llama-8B set 83.4% and 77.2% of
+// HBM peak; its rank-1-of-4 shard, whose tiles meet at most two segments,
+// 80.0% and 76.2%).
 template <bool kMixed>
 __global__ __launch_bounds__(kBlock) void scatter_layout(
     const uint8_t* __restrict__ span, const TileDev* __restrict__ tiles,
