@@ -130,6 +130,7 @@ struct ii_plan_s {
     // LayoutRow and a length
     std::vector<uint64_t> lstage;
     uint64_t* ldst() { return lstage.data(); }
+    const uint64_t* ldst() const { return lstage.data(); }
     const ii::LayoutRow* lrows() const {
         return reinterpret_cast<const ii::LayoutRow*>(lstage.data() + lseg.size());
     }

@@ -352,25 +352,35 @@ static LayoutTable layout_table(const ii_plan_t* p, uint8_t* at, const LayoutBlo
 // Form a plan's rows (and, unless tiles is null, its tiles' ranges) on the
 // device, ordered on `s`; with own_dst the rows go to the destinations in
 // p->ldst(), else they serve any arena. What they are formed from goes as
-// arguments of the kernel where it fits and else into `stage` by one copy
-// (each copy crosses to a copy engine and back, ~19 us between two kernels);
-// of a pageable source, so it returns once its bytes are staged. For failure
+// arguments of a few launches where it fits and else into `stage` by one
+// copy, of a pageable source, so it returns once its bytes are staged. For failure
 // injection rows and lengths are an upload each, whichever way they go.
 static int put_rows(const ii_plan_t* p, uint8_t* stage, LayoutSeg* rows, TileDev* tiles,
                     bool own_dst, hipStream_t s) {
     const uint32_t S = (uint32_t)p->lseg.size();
-    const uint64_t* words = p->lstage.data() + (own_dst ? 0 : S);
-    const uint64_t bytes = (own_dst ? 28ull : 20ull) * S;
+    const LayoutRow* lrows = p->lrows();
+    const uint32_t* llen = p->llen();
     II_HIP(injected(kSiteH2D) ? hipErrorUnknown : hipSuccess);
-    LayoutArgs args;
-    if (bytes <= sizeof args) {
+    const uint32_t most = sizeof(LayoutArgs) / (own_dst ? 28 : 20);  // segments a launch takes
+    if (S <= most * kByValueLaunches) {
         II_HIP(injected(kSiteH2D) ? hipErrorUnknown : hipSuccess);
-        memcpy(args.words, words, bytes);
-        II_HIP(launch_injected() ? hipErrorLaunchFailure
-                                 : launch_layout_tables_by_value(args, own_dst, S, p->tile_bytes,
-                                                                 rows, tiles, s));
+        for (uint32_t j = 0; j < S; j += most) {
+            const uint32_t n = std::min(most, S - j);
+            LayoutArgs args;
+            uint64_t* w = args.words;
+            if (own_dst) w = std::copy_n(p->ldst() + j, n, w);
+            memcpy(w, lrows + j, n * sizeof(LayoutRow));
+            memcpy(w + 2 * n, llen + j, n * sizeof(uint32_t));
+            II_HIP(launch_injected()
+                       ? hipErrorLaunchFailure
+                       : launch_layout_tables_by_value(
+                             args, own_dst, n, j, j ? lrows[j - 1].pos + llen[j - 1] : 0,
+                             j + n < S ? lrows[j + n].pos : ~0ull, p->tile_bytes, rows, tiles, s));
+        }
         return II_OK;
     }
+    const uint64_t* words = p->lstage.data() + (own_dst ? 0 : S);
+    const uint64_t bytes = (own_dst ? 28ull : 20ull) * S;
     II_HIP(h2d(stage, words, bytes, s));
     const uint64_t* dst = own_dst ? reinterpret_cast<const uint64_t*>(stage) : nullptr;
     const auto* from = reinterpret_cast<const LayoutRow*>(stage + (own_dst ? 8ull * S : 0));

@@ -405,26 +405,31 @@ __device__ __forceinline__ uint32_t table_segment() {
                  : blockIdx.x * kTableBlock + threadIdx.x;
 }
 
+// from, len and dst hold segments s0 .. s0 + n - 1 of the layout; `before`:
+// where the segment before them ends (0: none), `after`: where the one
+// behind them starts (all ones: none).
 template <bool kWave>
 __device__ __forceinline__ void form_tables(const LayoutRow* __restrict__ from,
                                             const uint32_t* __restrict__ len,
                                             const uint64_t* __restrict__ dst, uint32_t n,
+                                            uint32_t s0, uint64_t before, uint64_t after,
                                             uint32_t tile_bytes, uint32_t shift,
                                             LayoutSeg* __restrict__ rows,
                                             TileDev* __restrict__ tiles) {
     const uint32_t j = table_segment<kWave>();
     RowTiles t{1, 0, false, false};  // no tiles
+    rows += s0;
     if (j < n) {
         const LayoutRow r = from[j];
         const uint32_t l = len[j];
-        const uint64_t prev_end = j ? from[j - 1].pos + len[j - 1] : 0;
-        const uint64_t next_pos = j + 1 < n ? from[j + 1].pos : ~0ull;
+        const uint64_t prev_end = j ? from[j - 1].pos + len[j - 1] : before;
+        const uint64_t next_pos = j + 1 < n ? from[j + 1].pos : after;
         t = row_tiles(r.pos, l, prev_end, next_pos, tile_bytes, shift);
         if (blockIdx.y == 0 && (!kWave || (threadIdx.x & 63u) == 0))
             rows[j] = LayoutSeg{r.src, dst ? dst[j] : r.pos, r.pos, l, 0};
     }
     if (!tiles) return;
-    fill_tiles<kWave>(t, j < n, j, [&](const RowTiles& rt, uint32_t s, uint64_t m) {
+    fill_tiles<kWave>(t, j < n, s0 + j, [&](const RowTiles& rt, uint32_t s, uint64_t m) {
         if (m > rt.m0 || rt.first0) tiles[m].first = s;
         if (m < rt.m1 || rt.last1) tiles[m].last = s + 1;
     });
@@ -435,7 +440,7 @@ __global__ __launch_bounds__(kTableBlock) void layout_tables(
     const LayoutRow* __restrict__ from, const uint32_t* __restrict__ len,
     const uint64_t* __restrict__ dst, uint32_t n, uint32_t tile_bytes, uint32_t shift,
     LayoutSeg* __restrict__ rows, TileDev* __restrict__ tiles) {
-    form_tables<kWave>(from, len, dst, n, tile_bytes, shift, rows, tiles);
+    form_tables<kWave>(from, len, dst, n, 0, 0, ~0ull, tile_bytes, shift, rows, tiles);
 }
 
 // The ring's tables the same way: a tile's segments, and for plans with gaps
@@ -470,14 +475,17 @@ __global__ __launch_bounds__(kTableBlock) void ring_tables(const RingSeg* __rest
     });
 }
 
-// The layout tables with what the rows are formed from passed by value, in the order
-// destinations (if any), rows, lengths: a table of a small model needs no
-// upload (a copy from pageable memory takes the host 2.7 us for 512 bytes
-// and 4.4 us for 4 KiB, on top of the launch, and larger ones cross to a
-// copy engine and back, ~19 us of idle device each).
+// The layout tables with what the rows are formed from passed by value, in
+// the order destinations (if any), rows, lengths: a small table needs no
+// upload. A copy from pageable memory of more than 16 KiB crosses to a copy
+// engine and back, ~25 us between two kernels, and a smaller one takes the
+// host 2.7 us for 512 bytes and 8.8 us for 16 KiB; a launch with 3.5 KiB of
+// arguments takes the host 3.3 us, so up to kByValueLaunches of them go, one
+// behind the other, each with its share of the segments.
 __global__ __launch_bounds__(kTableBlock) void layout_tables_by_value(
-    LayoutArgs, uint32_t has_dst, uint32_t n, uint32_t tile_bytes, uint32_t shift,
-    LayoutSeg* __restrict__ rows, TileDev* __restrict__ tiles) {
+    LayoutArgs, uint32_t has_dst, uint32_t n, uint32_t s0, uint64_t before, uint64_t after,
+    uint32_t tile_bytes, uint32_t shift, LayoutSeg* __restrict__ rows,
+    TileDev* __restrict__ tiles) {
     // the first argument where it lies, at the start of the kernel's argument
     // segment: indexed as a variable it would be copied to scratch, 3.5 KiB a
     // lane (253 us)
@@ -485,7 +493,8 @@ __global__ __launch_bounds__(kTableBlock) void layout_tables_by_value(
     const uint64_t* const w = words + (has_dst ? n : 0);
     form_tables<true>(reinterpret_cast<const LayoutRow*>(w),
                       reinterpret_cast<const uint32_t*>(w + 2 * n),
-                      has_dst ? words : nullptr, n, tile_bytes, shift, rows, tiles);
+                      has_dst ? words : nullptr, n, s0, before, after, tile_bytes, shift, rows,
+                      tiles);
 }
 
 // Zero the byte ranges [r.begin, r.end) (device addresses). One workgroup per
@@ -584,14 +593,15 @@ hipError_t launch_ring_tables(const RingSeg* segs, uint32_t n, uint32_t tile_byt
 }
 
 hipError_t launch_layout_tables_by_value(const LayoutArgs& a, bool has_dst, uint32_t n,
+                                         uint32_t s0, uint64_t before, uint64_t after,
                                          uint32_t tile_bytes, LayoutSeg* rows, TileDev* tiles,
                                          hipStream_t stream) {
     if (n == 0) return hipSuccess;
     if ((has_dst ? 28ull : 20ull) * n > sizeof a) return hipErrorInvalidValue;
     const uint32_t gx = (n + 3) / 4;
     hipLaunchKernelGGL(layout_tables_by_value, dim3(gx, table_slices(gx, tiles)),
-                       dim3(kTableBlock), 0, stream, a, has_dst ? 1u : 0u, n, tile_bytes,
-                       tile_shift(tile_bytes), rows, tiles);
+                       dim3(kTableBlock), 0, stream, a, has_dst ? 1u : 0u, n, s0, before, after,
+                       tile_bytes, tile_shift(tile_bytes), rows, tiles);
     return hipGetLastError();
 }
 

@@ -35,12 +35,16 @@ hipError_t launch_layout_tables(const LayoutRow* from, const uint32_t* len, cons
                                 uint32_t n, uint32_t tile_bytes, LayoutSeg* rows, TileDev* tiles,
                                 uint64_t ntiles, hipStream_t stream);
 
-// The same for few segments, what the rows are formed from in the kernel's
-// arguments: n destinations if has_dst, n LayoutRows, n lengths.
+// The same for n segments from s0 on, what the rows are formed from in the
+// kernel's arguments: n destinations if has_dst, n LayoutRows, n lengths.
+// before: where segment s0 - 1 ends (0: none); after: where segment s0 + n
+// starts (all ones: none). tiles: of the whole layout, rows likewise.
 struct LayoutArgs {
     uint64_t words[448];  // 3.5 KiB: 179 segments, 128 with destinations
 };
+constexpr uint32_t kByValueLaunches = 4;
 hipError_t launch_layout_tables_by_value(const LayoutArgs& args, bool has_dst, uint32_t n,
+                                         uint32_t s0, uint64_t before, uint64_t after,
                                          uint32_t tile_bytes, LayoutSeg* rows, TileDev* tiles,
                                          hipStream_t stream);
 hipError_t launch_zero(const RangeDev* ranges, uint32_t n, hipStream_t stream);

@@ -101,6 +101,37 @@ def test_noalloc_sparse_layout(orc):
     _both(orc, synth.tiny(), s)
 
 
+@pytest.mark.parametrize("n", [1, 128, 129, 179, 180, 358, 359, 512, 513, 716, 717])
+def test_noalloc_table_sizes(orc, n):
+    """Tables around the sizes where what the rows are formed from goes in
+    one launch's arguments, in several launches' and by a copy, for one
+    arena (179 segments a launch) and for destinations of their own (128);
+    tensors of a few bytes to a few tiles, so that tiles reach across the
+    launches' shares."""
+    import oracle_pins
+    rng = np.random.default_rng(n)
+    sizes = [int(x) for x in np.exp(rng.uniform(0, np.log(40000), n)).astype(np.int64) + 1]
+    src = [int(x) for x in 5 + np.cumsum([0] + sizes[:-1])]
+    t = oracle_pins._u8_table(sizes, src, [int(a) for a in 1 << rng.integers(0, 5, n)])
+    plan = ii.ii_plan(t, 1 << 30)
+    assert plan.num_segments == n
+    blob = synth.blob(5 + sum(sizes), seed=n)
+    image = torch.from_numpy(blob).to(DEV)
+    _, off = plan.tensors()
+    # spread: every destination 16 bytes further from its place in the layout
+    for gap in (0, 16):
+        rel = off + np.arange(n, dtype=np.uint64) * np.uint64(gap)
+        arena = torch.full((int(rel[-1]) + sizes[-1] + 2048,), 0xA5, dtype=torch.uint8, device=DEV)
+        for load in (ii.ii_load_device_noalloc, ii.ii_load_device):
+            arena.fill_(0xA5)
+            load(plan, image, np.uint64(arena.data_ptr() + 1024) + rel)
+            want = np.full(arena.numel(), 0xA5, np.uint8)
+            for o, d in zip(orc.load(orc.nbytes(t), t.src_offset, blob), rel):
+                want[1024 + int(d):1024 + int(d) + o.size] = o
+            assert np.array_equal(arena.cpu().numpy(), want), (n, gap, load.__name__)
+    plan.free()
+
+
 def test_noalloc_refuses_tables_beyond_the_workspace():
     """The Llama-70B-shaped plan needs 275 MB of tile tables: refused with
     II_ESCRATCH before anything is checked or enqueued."""
