@@ -150,10 +150,11 @@ void ii_plan_free(ii_plan_t* plan);
  * device slot with one hipMemcpyAsync, then scatter it into its tensors
  * with the device kernel. A pinned blob's chunk skips the host slot: it is
  * copied straight from the blob. A pinned blob whose table has gaps between
- * segments, or at most 16 chunks, skips the chunks altogether: one launch on
- * `stream` reads the blob over the host link, as ii_load_device does from
- * pinned memory (a traced load runs the chunks all the same, its chunks with
- * gaps moved as ii_plan_copy_bytes says).
+ * segments, or at most 16 chunks and few small scattered tensors, skips the
+ * chunks altogether: one launch on `stream` reads the blob over the host
+ * link, as ii_load_device does from pinned memory (a traced load runs the
+ * chunks all the same, its chunks with gaps moved as ii_plan_copy_bytes
+ * says).
  * Chunks holding no segment are not touched. Chunk k's copy and scatter
  * run on lane k mod lanes (see ii_plan_set_ring), so with two or more lanes
  * chunk k+1's copy overlaps chunk k's scatter. A slot is
@@ -250,9 +251,13 @@ int ii_load_device(ii_plan_t* plan, const void* dev_image, uint64_t image_bytes,
  * the call allocates nothing -- no device or pinned host memory, no events,
  * streams or plan state. The kernel's tables (a 32-byte row per segment, an
  * 8-byte segment range per layout tile, and when some window of the layout
- * holds only padding a 4-byte window index per tile) are uploaded on every
- * call, on `stream`, into a static device workspace of 64 MiB that the
- * library holds on each GPU it runs on until the process ends; a plan whose
+ * holds only padding a 4-byte window index per tile) are formed on every
+ * call, on `stream`, in a static device workspace that the library holds on
+ * each GPU it runs on until the process ends: from 20 bytes per segment, or
+ * 28 where the destinations are not one arena of the plan's layout, uploaded
+ * or passed as kernel arguments (the ranges and windows of a layout with
+ * padding-only windows are uploaded as they are). The workspace has 64 MiB
+ * for the tables and 56 MiB for what they are formed from; a plan whose
  * tables need more returns II_ESCRATCH before anything is checked or
  * enqueued (the Llama-8B-shaped table needs 31 MB, the 100,000-tensor one
  * 5.1 MB). Calls
@@ -343,7 +348,7 @@ int ii_check_dst(const ii_plan_t* plan, void* const* dst_ptrs);
  * would otherwise allocate on first use: the staging ring (pinned host slots,
  * touched page by page so the first load does not fault them in; device
  * slots; streams; host copy threads) and the ring's device tables (the
- * resident-image kernel's tables are allocated by the first ii_load_device
+ * resident-image kernel's tables are allocated and formed by the first load
  * that needs them). Optional:
  * a cold-starting process can call it while other initialisation runs, so
  * the first load starts moving bytes at once (Sec. 4.2 overlaps independent
@@ -384,9 +389,8 @@ uint64_t ii_plan_chunk_bytes(const ii_plan_t* plan);
 uint64_t ii_plan_payload_bytes(const ii_plan_t* plan); /* sum of nbytes */
 uint64_t ii_plan_arena_bytes(const ii_plan_t* plan);
 /* bytes one load from a pinned blob moves from host to device through the
- * chunk pipeline (ii_switch, a traced ii_load, an ii_load of a table without
- * gaps and more than 16 chunks; an ii_load that reads the blob over the link
- * in one launch moves payload_bytes). A table
+ * chunk pipeline (ii_switch, a traced ii_load, an ii_load that does not read the
+ * blob over the link in one launch; one that does moves payload_bytes). A table
  * whose tensors tile their span: per chunk, its used range -- first
  * segment's start to last segment's end, rounded out to 256-byte boundaries
  * inside the chunk -- copied in place (hi - lo in all). A table with gaps
@@ -394,7 +398,8 @@ uint64_t ii_plan_arena_bytes(const ii_plan_t* plan);
  * when its runs (segments adjacent in the file, merged) form at most 2
  * groups of one run length and one spacing ($II_PINNED_GROUPS_MAX, 0..64)
  * -- each group is one 1-D or 2-D copy straight from the blob (the rows of
- * a column block) -- or when more than a quarter of its used range is gaps
+ * a column block; gathered on the host if they are not whole 4-byte words)
+ * -- or when more than a quarter of its used range is gaps
  * (it is then gathered on the host through the staging slot); otherwise its
  * used range in place. Loads from a pageable blob or a file gather every
  * chunk with gaps and move payload_bytes. */

@@ -138,6 +138,9 @@ struct ii_plan_s {
         return reinterpret_cast<const uint32_t*>(lstage.data() + 3 * lseg.size());
     }
     uint64_t nltiles = 0;
+    // bytes of the 128-byte source lines a kernel reads that walks the
+    // layout: lines that neighbouring segments share count once
+    uint64_t line_bytes = 0;
     // kept only for layouts with padding-only windows; otherwise tile g is
     // window g, and the ranges follow from the segments (row_tiles)
     std::vector<ii::TileDev> ltiles;

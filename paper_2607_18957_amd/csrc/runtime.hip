@@ -998,11 +998,14 @@ static int run_device(ii_plan_t* p, const uint8_t* image, const uint64_t* dst, h
 
 // Whether a load from a pinned blob goes by one launch that reads the blob
 // over the link (scatter_layout_link) instead of the chunk pipeline:
-//   tables with gaps, always: the pipeline's 2-D copies of their rows hold
-//     the calling thread for the whole transfer, and the copy engine moves
-//     rows that are not multiples of 4 bytes one by one (one rank of four of
-//     a 3.0 GB model, 749 MB: 13.75 -> 13.04 ms; 218 MB of 8-bit weights in
-//     rows of 1659 and 3473 bytes: 219 -> 4.0 ms);
+//   tables with gaps: the pipeline's 2-D copies of their rows hold the
+//     calling thread for the whole transfer, and its host gather copies short
+//     rows one by one (one rank of four of a 3.0 GB model, 749 MB: 13.6 ->
+//     13.04 ms; of smaller models in rows of 240, 482 and 964 bytes: 1060 ->
+//     624 us, 4.20 -> 2.33 and 5.09 -> 4.20 ms). The one kind measured that
+//     loses is a single chunk of some 10 MB loaded back to back from several
+//     plans, whose gather the pipeline hides behind the load before: 187 ->
+//     206 us (353 -> 218 when each load is waited for);
 //   others of at most kLinkChunks chunks: the pipeline's first copy and last
 //     scatter, its hand-overs and the copy engines' start-up are then a
 //     sizeable part (16.8 MB in 5 chunks: 378 -> 312 us with the host
@@ -1010,13 +1013,18 @@ static int run_device(ii_plan_t* p, const uint8_t* image, const uint64_t* dst, h
 //     3.50 ms). With more chunks the two are within 1.3% (3.0 GB in 45:
 //     52.8 and 52.1 ms; 948 MB in 57, permuted: 16.9 both), and the copy
 //     engines, which prefetch before the caller's earlier work is done,
-//     stay the path.
+//     stay the path. So they do where small tensors lie scattered: the link
+//     carries whole 128-byte lines, and where those come to more than 1.03
+//     times the payload the pipeline is level or ahead (tensors of 64-512
+//     bytes 133 and 105 us, 512-8192 bytes 1028 and 1012 us; of 528-33792
+//     bytes, lines 1.016 times the payload, 930 against 1005 us).
 // A traced load always runs the pipeline whose timeline it records.
 constexpr size_t kLinkChunks = 16;
 
 static bool reads_over_link(const ii_plan_t* p) {
     if (p->trace) return false;
-    return p->packed_distinct || p->num_chunks <= kLinkChunks;
+    if (p->packed_distinct) return true;
+    return p->num_chunks <= kLinkChunks && 100 * p->line_bytes <= 103 * p->payload;
 }
 
 static int run_pinned(ii_plan_t* p, const uint8_t* blob, const uint64_t* dst, hipStream_t stream) {

@@ -391,9 +391,32 @@ def test_pinned_blob_read_over_the_link(orc, tiles):
 
 
 def test_pinned_shard_of_odd_rows(orc):
-    """One rank's 8-bit weights in rows of 33 and 83 bytes, from a pinned blob."""
+    """One rank's 8-bit weights in rows of 33 and 83 bytes, from a pinned
+    blob: read over the link, and through the chunk pipeline (a switch),
+    which gathers rows that are not whole words."""
     t = synth.transformer_tp("odd", 2, 264, 664, 264, 512, 3, 8, dtype="fp8_e4m3", chunk=1 << 14)
-    _load_arena(orc, t, mode="pinned")
+    plan = _load_arena(orc, t, mode="pinned")
+    old = synth.transformer("old", 1, 64, 128, 64, 300, seed=8)
+    po = ii.ii_plan(old)
+    total = max(plan.arena_bytes, po.arena_bytes)
+    arena = torch.zeros(total, dtype=torch.uint8, device=DEV)
+    hb = ii.ii_host_alloc(t.blob_bytes)
+    hb.numpy()[:] = synth.blob(t)
+    ii.ii_switch(po, plan, arena, total, hb)
+    torch.cuda.synchronize()
+    want = _expect_arena(orc, t, synth.blob(t), np.zeros(plan.arena_bytes, np.uint8))
+    assert np.array_equal(arena.cpu().numpy()[:plan.arena_bytes], want)
+
+
+def test_pinned_small_scattered_tensors(orc):
+    """Tables without gaps on both sides of the rule on source lines: small
+    tensors in a permuted file (the chunk pipeline) and in file order (one
+    launch over the link)."""
+    _load_arena(orc, synth.stress(n=3000, lo_bytes=64, hi_bytes=512, header=3), mode="pinned")
+    sizes = [int(x) for x in np.random.default_rng(5).integers(64, 512, 3000)]
+    t = oracle_pins._u8_table(sizes, [int(x) for x in np.cumsum([3] + sizes[:-1])], [1] * 3000)
+    t.name, t.chunk_bytes = "in order", 1 << 18
+    _load_arena(orc, t, mode="pinned", blob=synth.blob(3 + sum(sizes), seed=5))
 
 
 def test_separate_tensor_buffers(orc):
