@@ -408,6 +408,27 @@ def test_pinned_shard_of_odd_rows(orc):
     assert np.array_equal(arena.cpu().numpy()[:plan.arena_bytes], want)
 
 
+def test_pinned_blob_rewritten_between_loads(orc):
+    """The host rewrites a pinned blob between loads that read it over the
+    link: each load sees the bytes written before it."""
+    for t in (synth.tiny(), synth.tiny_tp(1, 4)):
+        plan = ii.ii_plan(t)
+        _, off = plan.tensors()
+        hb = ii.ii_host_alloc(t.blob_bytes)
+        arena = torch.zeros(plan.arena_bytes, dtype=torch.uint8, device=DEV)
+        for k in range(6):
+            blob = synth.blob(t.blob_bytes, seed=100 + k)
+            hb.numpy()[:] = blob
+            if k % 2:
+                ii.ii_load(plan, hb, arena.data_ptr() + off)
+            else:
+                ii.ii_load_device(plan, (hb.ptr, hb.nbytes), arena.data_ptr() + off)
+            torch.cuda.synchronize()
+            want = _expect_arena(orc, t, blob, np.zeros(plan.arena_bytes, np.uint8))
+            assert np.array_equal(arena.cpu().numpy(), want), k
+        plan.free()
+
+
 def test_pinned_small_scattered_tensors(orc):
     """Tables without gaps on both sides of the rule on source lines: small
     tensors in a permuted file (the chunk pipeline) and in file order (one
