@@ -313,6 +313,7 @@ extern "C" int ii_plan(const ii_tensor_desc* table, size_t n, uint64_t chunk_byt
         // (measured on tensor-parallel shards: up to 2 groups beats both
         // the host gather and 8 groups).
         p->chunk_pinned.assign(p->num_chunks, kPinnedInPlace);
+        p->chunk_words.assign(p->num_chunks, 1);
         if (p->packed_distinct) p->chunk_group_begin.assign(p->num_chunks + 1, 0);
         const uint32_t max_groups = env_u32("II_PINNED_GROUPS_MAX", kMaxDmaGroups, 0, 64);
         for (size_t k = 0; k < p->num_chunks; ++k) {
@@ -336,17 +337,15 @@ extern "C" int ii_plan(const ii_tensor_desc* table, size_t n, uint64_t chunk_byt
                 p->groups.push_back(g);
                 r = q;
             }
-            // The copy engine moves rows that are not whole 4-byte words one
-            // by one (218 MB in rows of 1659 and 3473 bytes: 219 ms, 4 ms
-            // gathered): those are gathered.
             bool words = true;
             for (size_t g = g0; g < p->groups.size(); ++g) {
                 const DmaGroup& x = p->groups[g];
                 words &= x.count == 1 || !((p->lo + k * C + x.off) & 3 || x.len & 3 ||
                                            x.stride & 3 || x.poff & 3);
             }
+            p->chunk_words[k] = words;
             uint8_t how = kPinnedInPlace;
-            if (p->groups.size() - g0 <= max_groups) how = words ? kPinnedGroups : kPinnedGather;
+            if (p->groups.size() - g0 <= max_groups) how = kPinnedGroups;
             else if (4 * (e - b - p->chunk_plen[k]) > (e - b)) how = kPinnedGather;
             if (how != kPinnedGroups) p->groups.resize(g0);
             p->chunk_group_begin[k + 1] = p->groups.size();

@@ -842,7 +842,8 @@ static int run_ring(ii_plan_t* p, const Source& src, const uint64_t* dst, hipStr
         const uint64_t at = cbeg + u0;                   // ... and of its used range
         // a pinned blob's chunk of a plan with gaps: moved in place, by
         // copies of its run groups, or gathered on the host
-        const uint8_t how = pinned && p->packed_distinct ? p->chunk_pinned[k] : kPinnedInPlace;
+        uint8_t how = pinned && p->packed_distinct ? p->chunk_pinned[k] : kPinnedInPlace;
+        if (how == kPinnedGroups && !p->chunk_words[k]) how = kPinnedGather;
         const bool packed = p->packed_distinct && (!pinned || how != kPinnedInPlace);
         const bool staged = !pinned || how == kPinnedGather;  // through the pinned slot
         // packed: the slot receives the chunk's runs back to back from offset

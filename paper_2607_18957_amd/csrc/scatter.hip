@@ -13,8 +13,9 @@
 // Llama-8B-shaped set against 256 threads x 8 KiB, 64 x 2 KiB, 8 and 16 KiB
 // tiles, four or eight units per lane and persistent grids of 8 or 16
 // workgroups per CU: two units per lane in small workgroups, one tile each,
-// is fastest. The planner stores, per tile, the segment rows whose bytes
-// meet it, so a workgroup reads only its own rows.
+// is fastest. Per tile a table holds the range of segment rows whose bytes
+// meet it (layout_tables, ring_tables), so a workgroup reads only its own
+// rows.
 //   Ring (scatter_slot): a staged chunk's segment bytes are cut in segment
 // order, gaps between segments skipped, so no workgroup exists for bytes no
 // tensor needs (the gaps a sharded table leaves in the file). In a packed
@@ -29,7 +30,8 @@
 // misaligned reads cost nothing measurable, so cutting by destination wins
 // wherever source and destination offsets are not congruent modulo the
 // tile (the 100,000-tensor set: 5.43 against 5.09 TB/s) and ties where
-// they are (the Llama sets).
+// they are (the Llama sets). An image in pinned host memory is read over the
+// link by few workgroups that walk the same tiles (scatter_layout_link).
 //
 // Units. Destination memory is written in 16-byte blocks aligned to 16
 // bytes, so every store of a block that a segment covers completely is one
@@ -138,8 +140,9 @@ __device__ __forceinline__ uint32_t wave_scan(uint32_t v) {
 // Measured: on tables of large tensors, where a tile is one unbroken 4 KiB
 // stream, the first is faster (83.4% against 77.2% of HBM peak on a
 // Llama-8B-shaped set); more loads in flight only lengthen the queues. On
-// the 100,000-tensor set, whose tiles spend longer forming rows, the second
-// is (68.1% against 65.7%).
+// the 100,000-tensor set, a tenth of whose tiles meet three segments or more
+// and spend longer forming rows, the second is for those (all tiles one unit
+// at a time 326.0 us, only tiles of one segment 322.0).
 template <bool kOverlap, class RowAt>
 __device__ __forceinline__ void move_units(DevMem& mem, uint32_t base, uint32_t total,
                                            RowAt row_at) {
