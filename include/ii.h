@@ -167,6 +167,8 @@ void ii_plan_free(ii_plan_t* plan);
  *               device slots of chunk_bytes each (default depth 3, see
  *               ii_plan_set_ring) plus the plan's device tables; they are
  *               kept for later loads until ii_plan_release / ii_plan_free.
+ *               A load that reads a pinned blob over the link allocates
+ *               its kernel's tables instead of the ring.
  *   host_blob   host address of blob byte 0. Pageable or pinned. Pageable
  *               blobs are read only during the call; a pinned blob
  *               (hipHostMalloc / ii_host_alloc) is read by DMA after the call
@@ -327,7 +329,8 @@ int ii_switch(const ii_plan_t* plan_old, ii_plan_t* plan_new, void* arena, uint6
  * one chunk overlaps the scatter of another, and a slot whose next chunk
  * runs on another lane is handed over by an event. Each lane's first copy
  * of a load may run before the work the caller enqueued ahead of it.
- * Errors: II_EINVAL (out of range), II_EBUSY (ring already allocated).
+ * Errors: II_EINVAL (out of range), II_EBUSY (ring already allocated, or a
+ * load from host memory has run).
  */
 int ii_plan_set_ring(ii_plan_t* plan, uint32_t depth, uint32_t host_threads,
                      uint32_t copy_streams);

@@ -353,8 +353,9 @@ static LayoutTable layout_table(const ii_plan_t* p, uint8_t* at, const LayoutBlo
 // device, ordered on `s`; with own_dst the rows go to the destinations in
 // p->ldst(), else they serve any arena. What they are formed from goes as
 // arguments of a few launches where it fits and else into `stage` by one
-// copy, of a pageable source, so it returns once its bytes are staged. For failure
-// injection rows and lengths are an upload each, whichever way they go.
+// copy, of a pageable source, so it returns once its bytes are staged. For
+// failure injection rows and lengths are an upload each, whichever way they
+// go.
 static int put_rows(const ii_plan_t* p, uint8_t* stage, LayoutSeg* rows, TileDev* tiles,
                     bool own_dst, hipStream_t s) {
     const uint32_t S = (uint32_t)p->lseg.size();
