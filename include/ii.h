@@ -174,15 +174,17 @@ void ii_plan_free(ii_plan_t* plan);
  *               (hipHostMalloc / ii_host_alloc) is read by DMA after the call
  *               returns and must stay valid and unchanged until `stream`
  *               reaches the point after this call. A blob counts as pinned
- *               when the first and the last byte of the span [lo, hi) are
- *               pinned; otherwise it is handled as pageable.
+ *               when its span [lo, hi) lies inside one pinned allocation;
+ *               otherwise it is handled as pageable. Memory pinned by
+ *               hipHostRegister that the device sees at another address is
+ *               only ever read by copies.
  *   blob_bytes  size of the blob; must be >= the plan's span end hi.
  *   dst_ptrs    n device addresses, one per table row (NULL allowed only for
  *               zero-size tensors); dst_ptrs[i] must be a multiple of
  *               dst_align[i]; the ranges [dst_ptrs[i], +nbytes[i]) must not
  *               overlap, and each must lie inside one device allocation or
- *               in pinned host memory (checked, II_EINVAL; see
- *               ii_check_dst). Read during the call only; the memory they
+ *               in pinned host memory that the device sees at the same
+ *               address (checked, II_EINVAL; see ii_check_dst). Read during the call only; the memory they
  *               point to must stay allocated until `stream` passes this
  *               call.
  *   stream      HIP stream (0 = null stream). Writes into the destinations
@@ -230,8 +232,9 @@ int ii_load_file(ii_plan_t* plan, int fd, uint64_t file_bytes, void* const* dst_
  *
  *   dev_image    device address of blob byte 0 (any alignment); the span
  *                [dev_image + lo, + hi) must lie inside one device allocation
- *                or in pinned host memory (checked, II_EINVAL). From pinned
- *                host memory the kernel reads the blob over the host link
+ *                or in pinned host memory that the device sees at the same
+ *                address, as hipHostMalloc and ii_host_alloc give it (checked,
+ *                II_EINVAL). From pinned host memory the kernel reads the blob over the host link
  *                itself: no ring and no copy engine, one launch of at most
  *                256 workgroups that walk the windows in order -- the
  *                lowest latency for small loads, and the link's rate for

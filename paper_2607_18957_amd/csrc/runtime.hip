@@ -489,6 +489,7 @@ static AllocInfo alloc_info(uint64_t x) {
         info.kind = AllocInfo::kPinnedHost;
     else
         return info;
+    info.device_at = reinterpret_cast<uint64_t>(a.devicePointer);
     hipDeviceptr_t base = nullptr;
     size_t size = 0;
     if (hipMemGetAddressRange(&base, &size, reinterpret_cast<hipDeviceptr_t>(x)) != hipSuccess) {
@@ -501,20 +502,23 @@ static AllocInfo alloc_info(uint64_t x) {
     return info;
 }
 
-// Whether the device can reach [b, e): the whole range inside one device
-// allocation or one pinned host allocation (reach.h). A kernel or a DMA
-// touching pageable memory, unknown memory, or a range that runs from one
-// allocation into whatever lies past its end would fault the device.
+// Whether kernels can reach [b, e): the whole range inside one device
+// allocation or one pinned host allocation that the device sees at the same
+// address (reach.h). A kernel or a DMA touching pageable memory, unknown
+// memory, or a range that runs from one allocation into whatever lies past
+// its end would fault the device.
 static bool accessible(uint64_t b, uint64_t e, AllocInfo* info = nullptr) {
     const AllocInfo a = alloc_info(b);
     if (info) *info = a;
     return reachable(a, b, e);
 }
 
-// Every range (sorted by address) reachable by the device: one allocation
-// query per allocation the ranges fall in.
-static int check_reach(const std::vector<DstRange>& v) {
-    const size_t j = first_unreachable(v, alloc_info);
+// Every range (sorted by address) reachable by the device, by kernels or (may
+// = copyable) by copies: one allocation query per allocation the ranges fall
+// in.
+static int check_reach(const std::vector<DstRange>& v,
+                       bool (*may)(const AllocInfo&, uint64_t, uint64_t) = reachable) {
+    const size_t j = first_unreachable(v, alloc_info, may);
     if (j == v.size()) return II_OK;
     return fail(II_EINVAL, "dst_ptrs[%zu]=%#llx (+%llu bytes) is not memory the device can "
                 "write: not inside one device allocation or one pinned host allocation",
@@ -522,13 +526,14 @@ static int check_reach(const std::vector<DstRange>& v) {
 }
 
 // Check destination addresses: present, aligned, pairwise disjoint and
-// reachable by the device.
-static int check_dst(const ii_plan_t* p, const uint64_t* dst) {
+// reachable by the device (see check_reach).
+static int check_dst(const ii_plan_t* p, const uint64_t* dst,
+                     bool (*may)(const AllocInfo&, uint64_t, uint64_t) = reachable) {
     uint64_t base, end;
     if (arena_base(p, dst, &base, &end) && accessible(base, end)) return II_OK;
     std::vector<DstRange> v;
     int rc = dst_ranges(p, dst, &v);
-    return rc ? rc : check_reach(v);
+    return rc ? rc : check_reach(v, may);
 }
 
 // No destination may overlap the source image [b, e) (one linear pass).
@@ -695,17 +700,15 @@ static int launch_scrub(ii_plan_t* p, const std::vector<RangeDev>& ranges, hipSt
     return II_OK;
 }
 
-// Whether the blob bytes a load reads, [blob + lo, blob + hi), lie inside one
-// pinned host allocation, so that copies may read them by DMA. A blob pinned
-// only in part (or whose span reaches past its pinned allocation) is treated
-// as pageable: the host stage copies it, and no DMA reads outside pinned
-// memory.
-static bool pinned_span(const ii_plan_t* p, const uint8_t* blob) {
-    if (p->hi <= p->lo) return false;
+// How the blob bytes a load reads, [blob + lo, blob + hi), may be read. A blob
+// pinned only in part (or whose span reaches past its pinned allocation) is
+// treated as pageable: the host stage copies it, and no DMA reads outside
+// pinned memory.
+static BlobKind blob_kind(const ii_plan_t* p, const uint8_t* blob) {
+    if (p->hi <= p->lo) return BlobKind::kPageable;
     const uint64_t b = reinterpret_cast<uint64_t>(blob) + p->lo;
     const uint64_t e = reinterpret_cast<uint64_t>(blob) + p->hi;
-    const AllocInfo a = alloc_info(b);
-    return a.kind == AllocInfo::kPinnedHost && reachable(a, b, e);
+    return blob_kind(alloc_info(b), b, e);
 }
 
 static bool is_device_ptr(const void* ptr) {
@@ -765,7 +768,7 @@ static int run_ring(ii_plan_t* p, const Source& src, const uint64_t* dst, hipStr
     if (rc) return rc;
     Runtime* r = p->rt;
     const uint8_t* blob = src.blob;
-    const bool pinned = src.fd < 0 && pinned_span(p, blob);
+    const bool pinned = src.fd < 0 && blob_kind(p, blob) != BlobKind::kPageable;
     // The host stage gathers packed chunks whenever it copies anyway, and
     // for a pinned blob also where most of a chunk's used range is gaps.
 
@@ -961,7 +964,7 @@ static hipError_t scatter_image(const ii_plan_t* p, const uint8_t* image, const 
 
 // One launch on `stream` over the whole table. image_b..image_e: the image's
 // span when it is checked here (reachable, disjoint from the destinations),
-// empty when the caller knows it to be pinned host memory.
+// empty when the caller knows it to be pinned host memory kernels can read.
 static int run_image(ii_plan_t* p, const uint8_t* image, const uint64_t* dst, hipStream_t stream,
                      uint64_t image_b, uint64_t image_e) {
     int rc = ensure_state(p);
@@ -1117,9 +1120,9 @@ static int run_pertensor(ii_plan_t* p, const uint8_t* blob, const uint64_t* dst,
     rc = ensure_ring(p);
     if (rc) return rc;
     Runtime* r = p->rt;
-    rc = check_dst(p, dst);
+    rc = check_dst(p, dst, copyable);
     if (rc) return rc;
-    const bool pinned = pinned_span(p, blob);
+    const bool pinned = blob_kind(p, blob) != BlobKind::kPageable;
     hipStream_t cs = r->lane_s[0];
     II_HIP(hipEventRecord(r->entry, stream));
     II_HIP(hipStreamWaitEvent(cs, r->entry, 0));
@@ -1205,8 +1208,8 @@ extern "C" int ii_load(ii_plan_t* p, const void* host_blob, uint64_t blob_bytes,
     Source src;
     src.blob = static_cast<const uint8_t*>(host_blob);
     const uint64_t* dst = reinterpret_cast<const uint64_t*>(dst_ptrs);
-    int rc = reads_over_link(p) && pinned_span(p, src.blob) ? run_pinned(p, src.blob, dst, stream)
-                                                            : run_ring(p, src, dst, stream, nullptr);
+    const bool link = reads_over_link(p) && blob_kind(p, src.blob) == BlobKind::kMapped;
+    int rc = link ? run_pinned(p, src.blob, dst, stream) : run_ring(p, src, dst, stream, nullptr);
     return rc ? drain(p, stream, rc) : II_OK;
 }
 
