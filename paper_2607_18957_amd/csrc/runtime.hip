@@ -139,9 +139,10 @@ struct Runtime {
     // rows with resolved destinations, for tensors that are not one arena,
     // and what they are formed from; one allocation
     LayoutSeg* d_lown = nullptr;
-    hipEvent_t lown_idle = nullptr;       // after the last kernel that read d_lown
-    hipStream_t lown_stream = nullptr;    // ... its stream (compared, never used)
-    bool lown_used = false, lown_mixed = false;  // read at all, from several streams
+    // After the last kernel that read d_lown. Every use waits for it first and
+    // records it again, so it covers all of them, whatever their streams.
+    hipEvent_t lown_idle = nullptr;
+    bool lown_used = false;
     bool image_used = false;              // an image kernel may be in flight
     // the ring's rows: read and written on the lanes, joined by lane 0
     hipEvent_t segs_uploaded = nullptr;   // after the last read of h_segs / h_psegs
@@ -151,7 +152,7 @@ struct Runtime {
     std::vector<uint64_t> cached_dst;
     std::vector<DstRange> cached_ranges;
     bool cached_valid = false;
-    bool lown_ok = false;                 // d_lown holds cached_dst's rows
+    bool lown_ok = false;                 // d_lown holds cached_dst's rows at lown_idle
     enum RingRows { kNoRows, kLayoutPos, kResolved } ring_rows = kNoRows;  // d_segs' dst fields
     uint64_t image_b = 0, image_e = 0;  // source image range last checked against cached_dst
     // scrub ranges
@@ -653,25 +654,32 @@ static void layout_dst(const ii_plan_t* p, const uint64_t* dst, uint64_t* out) {
     }
 }
 
-// Make d_lown hold destinations that are not one arena, written on `s` after
-// every kernel that read the previous ones.
-static int image_own_rows(ii_plan_t* p, const uint64_t* dst, hipStream_t s) {
+static bool capturing(hipStream_t s) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return st != hipStreamCaptureStatusNone;
+}
+
+// Make d_lown hold destinations that are not one arena for the work enqueued
+// next on `s`: ordered after the work that formed or read its rows, on
+// whichever stream (a wait for an event of the same stream does nothing).
+// Rows formed while `s` is being captured are formed when the graph runs, so
+// no later load may count on them; and a capture cannot wait for an event of
+// the streams outside it.
+static int image_own_rows(ii_plan_t* p, const uint64_t* dst, hipStream_t s, bool captured) {
     Runtime* r = p->rt;
     const size_t S = p->seg_len.size();
-    if (!S || r->lown_ok) return II_OK;
     if (!r->d_lown) II_HIP(dev_alloc(&r->d_lown, S * (sizeof(LayoutSeg) + 28)));
-    if (r->lown_used) {
-        if (r->lown_mixed) II_HIP(hipDeviceSynchronize());  // the event covers one stream
-        else II_HIP(hipStreamWaitEvent(s, r->lown_idle, 0));
-        r->lown_mixed = false;
-    }
+    if (r->lown_used && !captured) II_HIP(hipStreamWaitEvent(s, r->lown_idle, 0));
+    if (r->lown_ok) return II_OK;
     layout_dst(p, dst, p->ldst());
     const int rc = put_rows(p, reinterpret_cast<uint8_t*>(r->d_lown + S), r->d_lown, nullptr, true,
                             s);
     if (rc) return rc;
-    II_HIP(hipEventRecord(r->lown_idle, s));
-    r->lown_stream = s;
-    r->lown_used = r->lown_ok = true;
+    r->lown_ok = !captured;
     return II_OK;
 }
 
@@ -978,8 +986,9 @@ static int run_image(ii_plan_t* p, const uint8_t* image, const uint64_t* dst, hi
     rc = check_load(p, dst, image_b, image_e, &info, &to);
     if (rc) return rc;
     if (p->lseg.empty()) return II_OK;  // nothing to move
+    const bool captured = !to.arena && capturing(stream);
     if (!to.arena) {
-        rc = image_own_rows(p, dst, stream);
+        rc = image_own_rows(p, dst, stream, captured);
         if (rc) return rc;
     }
     const LayoutBlock l = layout_block(p);
@@ -988,10 +997,9 @@ static int run_image(ii_plan_t* p, const uint8_t* image, const uint64_t* dst, hi
         to.arena ? reinterpret_cast<const LayoutSeg*>(r->d_layout + l.rows) : r->d_lown);
     r->image_used = true;
     II_HIP(scatter_image(p, image, t, to.base, info.kind, stream));
-    if (!to.arena) {
-        r->lown_mixed |= r->lown_stream != stream;
-        r->lown_stream = stream;
+    if (!to.arena && !captured) {
         II_HIP(hipEventRecord(r->lown_idle, stream));
+        r->lown_used = true;
     }
     return II_OK;
 }

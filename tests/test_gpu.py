@@ -502,6 +502,71 @@ def test_arenas_and_own_destinations_in_turn(orc, dst_align):
     plan.free()
 
 
+@pytest.mark.parametrize("n", [40, 3000], ids=["rows-as-arguments", "rows-uploaded"])
+def test_own_destinations_across_streams(orc, n):
+    """Loads into destinations of their own on two streams that the caller
+    does not order, one of them behind pending work: the rows the kernel
+    reads are formed on the first call's stream, and a load on the other
+    stream -- of the same destinations, of new ones, of the first again --
+    must neither read them earlier nor rewrite them under a kernel. Every
+    load of one set of destinations has the same image, so any order gives
+    the same bytes."""
+    t = synth.stress(n=n, chunk=1 << 18)
+    plan = ii.ii_plan(t)
+    _, off = plan.tensors()
+    blob = synth.blob(t)
+    image = torch.from_numpy(blob).to(DEV)
+    tensors = orc.load(orc.nbytes(t), t.src_offset, blob)
+    sets = []
+    for k in range(3):
+        rel = off + np.arange(t.n, dtype=np.uint64) * np.uint64(256 * (k + 1))
+        arena = torch.full((int(rel[-1]) + tensors[-1].size + 2048,), 0xA5, dtype=torch.uint8,
+                           device=DEV)
+        sets.append((rel, arena, np.uint64(arena.data_ptr() + 1024) + rel))
+    a, b = torch.cuda.Stream(DEV), torch.cuda.Stream(DEV)
+
+    def check(which):
+        torch.cuda.synchronize()
+        for k in which:
+            rel, arena, _ = sets[k]
+            want = np.full(arena.numel(), 0xA5, np.uint8)
+            for o, d in zip(tensors, rel):
+                want[1024 + int(d):1024 + int(d) + o.size] = o
+            assert np.array_equal(arena.cpu().numpy(), want), k
+
+    warm = torch.empty(plan.arena_bytes, dtype=torch.uint8, device=DEV)
+    ii.ii_load_device(plan, image, warm.data_ptr() + off, b)
+    torch.cuda.synchronize()  # the plan's own tables are there
+    for first, second in ((a, b), (b, a)):
+        with torch.cuda.stream(first):
+            _busy(8)
+        ii.ii_load_device(plan, image, sets[0][2], first)   # formed behind the pending work
+        ii.ii_load_device(plan, image, sets[0][2], second)  # the same rows
+        ii.ii_load_device(plan, image, sets[1][2], second)  # new rows over them
+        ii.ii_load_device(plan, image, sets[0][2], first)
+        check([0, 1])
+        for _, arena, _ in sets:
+            arena.fill_(0xA5)
+        torch.cuda.synchronize()
+
+    # rows formed in a captured load exist only once the graph has run
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        ii.ii_load_device(plan, image, sets[2][2], torch.cuda.current_stream(DEV))
+    ii.ii_load_device(plan, image, sets[2][2], b)
+    check([2])
+    for _ in range(3):
+        sets[2][1].fill_(0xA5)
+        torch.cuda.synchronize()
+        g.replay()
+        check([2])
+        sets[2][1].fill_(0xA5)
+        torch.cuda.synchronize()
+        ii.ii_load_device(plan, image, sets[2][2], a)
+        check([2])
+    plan.free()
+
+
 @pytest.mark.parametrize("depth,copy_streams", [(1, 1), (2, 1), (2, 2), (3, 2), (3, 3), (4, 4)])
 def test_ring_race_stress(orc, depth, copy_streams):
     """Slot reuse under pressure (the data-safety rule of Sec. 4.2): 4 KiB
