@@ -244,6 +244,11 @@ int ii_load_file(ii_plan_t* plan, int fd, uint64_t file_bytes, void* const* dst_
  *   stream       the kernel runs on this stream, after the work already on
  *                it. The caller keeps the image and destinations alive
  *                until the stream passes this call.
+ * Under stream capture (once a call outside one has allocated the plan's
+ * tables): the graph reads those tables, so the plan must outlive it; and
+ * where the destinations are not one arena of the plan's layout, it may read
+ * the rows of the plan's last load of that kind, so no other destinations of
+ * that kind may be loaded between capture and replay.
  * Errors: as ii_load.
  */
 int ii_load_device(ii_plan_t* plan, const void* dev_image, uint64_t image_bytes,
@@ -270,6 +275,12 @@ int ii_load_device(ii_plan_t* plan, const void* dev_image, uint64_t image_bytes,
  * safe, calls that overlap on different streams of one GPU race (the later
  * upload may overwrite tables an earlier kernel still reads) and must be
  * ordered by the caller.
+ * Under stream capture (replays are calls as above): the graph uploads from
+ * the plan's own memory again at every replay, so the plan must live as long
+ * as the graph; and a table of more than 512 segments whose destinations are
+ * not one arena of the plan's layout goes, at replay, to the destinations of
+ * the plan's last call of ii_load_device_noalloc of that kind, so none with
+ * other destinations may come between.
  * Errors: as ii_load_device, plus II_ESCRATCH.
  */
 int ii_load_device_noalloc(ii_plan_t* plan, const void* dev_image, uint64_t image_bytes,

@@ -139,6 +139,11 @@ struct Runtime {
     // rows with resolved destinations, for tensors that are not one arena,
     // and what they are formed from; one allocation
     LayoutSeg* d_lown = nullptr;
+    // pinned staging for what they are formed from (tables too large for
+    // kernel arguments), and the event after the last upload that read it
+    uint64_t* h_lown = nullptr;
+    hipEvent_t lown_sent = nullptr;
+    bool lown_staged = false;
     // After the last kernel that read d_lown. Every use waits for it first and
     // records it again, so it covers all of them, whatever their streams.
     hipEvent_t lown_idle = nullptr;
@@ -246,11 +251,13 @@ static void destroy(Runtime* r) {
     if (r->d_wins) (void)hipFree(r->d_wins);
     if (r->d_layout) (void)hipFree(r->d_layout);
     if (r->d_lown) (void)hipFree(r->d_lown);
+    if (r->h_lown) (void)hipHostFree(r->h_lown);
     if (r->d_psegs) (void)hipFree(r->d_psegs);
     if (r->h_psegs) (void)hipHostFree(r->h_psegs);
     if (r->d_ranges) (void)hipFree(r->d_ranges);
     if (r->h_ranges) (void)hipHostFree(r->h_ranges);
     if (r->lown_idle) (void)hipEventDestroy(r->lown_idle);
+    if (r->lown_sent) (void)hipEventDestroy(r->lown_sent);
     if (r->segs_uploaded) (void)hipEventDestroy(r->segs_uploaded);
     if (r->ranges_idle) (void)hipEventDestroy(r->ranges_idle);
     (void)hipGetLastError();
@@ -278,7 +285,7 @@ static int ensure_state(ii_plan_t* p) {
     if (r->device != dev)
         return fail(II_EINVAL, "plan was first used on device %d, current device is %d",
                     r->device, dev);
-    for (hipEvent_t* e : {&r->lown_idle, &r->segs_uploaded, &r->ranges_idle})
+    for (hipEvent_t* e : {&r->lown_idle, &r->lown_sent, &r->segs_uploaded, &r->ranges_idle})
         if (!*e) II_HIP(hipEventCreateWithFlags(e, hipEventDisableTiming));
     if (!r->live_ready) {
         r->live.clear();
@@ -350,27 +357,34 @@ static LayoutTable layout_table(const ii_plan_t* p, uint8_t* at, const LayoutBlo
                        p->nltiles, rows};
 }
 
+// Segments whose rows one launch forms from its arguments, and whether a
+// plan's are few enough to go that way.
+static uint32_t by_value_most(bool own_dst) { return sizeof(LayoutArgs) / (own_dst ? 28 : 20); }
+static bool fits_by_value(const ii_plan_t* p, bool own_dst) {
+    return p->lseg.size() <= by_value_most(own_dst) * kByValueLaunches;
+}
+
 // Form a plan's rows (and, unless tiles is null, its tiles' ranges) on the
-// device, ordered on `s`; with own_dst the rows go to the destinations in
-// p->ldst(), else they serve any arena. What they are formed from goes as
-// arguments of a few launches where it fits and else into `stage` by one
-// copy, of a pageable source, so it returns once its bytes are staged. For
-// failure injection rows and lengths are an upload each, whichever way they
-// go.
-static int put_rows(const ii_plan_t* p, uint8_t* stage, LayoutSeg* rows, TileDev* tiles,
-                    bool own_dst, hipStream_t s) {
+// device, ordered on `s`, from what `words` holds laid out as p->lstage: with
+// own_dst destinations, LayoutRows and lengths, else LayoutRows and lengths
+// of rows that serve any arena. It goes as arguments of launches where by_value
+// says so and else into `stage` by one copy; of a pageable source that
+// returns once its bytes are staged. For failure injection rows and lengths
+// are an upload each, whichever way they go.
+static int put_rows(const ii_plan_t* p, const uint64_t* words, uint8_t* stage, LayoutSeg* rows,
+                    TileDev* tiles, bool own_dst, bool by_value, hipStream_t s) {
     const uint32_t S = (uint32_t)p->lseg.size();
     const LayoutRow* lrows = p->lrows();
     const uint32_t* llen = p->llen();
     II_HIP(injected(kSiteH2D) ? hipErrorUnknown : hipSuccess);
-    const uint32_t most = sizeof(LayoutArgs) / (own_dst ? 28 : 20);  // segments a launch takes
-    if (S <= most * kByValueLaunches) {
+    if (by_value) {
+        const uint32_t most = by_value_most(own_dst);
         II_HIP(injected(kSiteH2D) ? hipErrorUnknown : hipSuccess);
         for (uint32_t j = 0; j < S; j += most) {
             const uint32_t n = std::min(most, S - j);
             LayoutArgs args;
             uint64_t* w = args.words;
-            if (own_dst) w = std::copy_n(p->ldst() + j, n, w);
+            if (own_dst) w = std::copy_n(words + j, n, w);
             memcpy(w, lrows + j, n * sizeof(LayoutRow));
             memcpy(w + 2 * n, llen + j, n * sizeof(uint32_t));
             II_HIP(launch_injected()
@@ -381,7 +395,6 @@ static int put_rows(const ii_plan_t* p, uint8_t* stage, LayoutSeg* rows, TileDev
         }
         return II_OK;
     }
-    const uint64_t* words = p->lstage.data() + (own_dst ? 0 : S);
     const uint64_t bytes = (own_dst ? 28ull : 20ull) * S;
     II_HIP(h2d(stage, words, bytes, s));
     const uint64_t* dst = own_dst ? reinterpret_cast<const uint64_t*>(stage) : nullptr;
@@ -401,8 +414,10 @@ static int put_layout(const ii_plan_t* p, uint8_t* at, const LayoutBlock& l, boo
         II_HIP(h2d(at + l.tiles, p->ltiles.data(), p->ltiles.size() * sizeof(TileDev), s));
         II_HIP(h2d(at + l.win, p->lwin.data(), p->lwin.size() * sizeof(uint32_t), s));
     }
-    return put_rows(p, at + l.stage, reinterpret_cast<LayoutSeg*>(at + l.rows),
-                    listed ? nullptr : reinterpret_cast<TileDev*>(at + l.tiles), own_dst, s);
+    return put_rows(p, p->lstage.data() + (own_dst ? 0 : p->lseg.size()), at + l.stage,
+                    reinterpret_cast<LayoutSeg*>(at + l.rows),
+                    listed ? nullptr : reinterpret_cast<TileDev*>(at + l.tiles), own_dst,
+                    fits_by_value(p, own_dst), s);
 }
 
 static int ensure_layout_tables(ii_plan_t* p) {
@@ -675,10 +690,37 @@ static int image_own_rows(ii_plan_t* p, const uint64_t* dst, hipStream_t s, bool
     if (!r->d_lown) II_HIP(dev_alloc(&r->d_lown, S * (sizeof(LayoutSeg) + 28)));
     if (r->lown_used && !captured) II_HIP(hipStreamWaitEvent(s, r->lown_idle, 0));
     if (r->lown_ok) return II_OK;
-    layout_dst(p, dst, p->ldst());
-    const int rc = put_rows(p, reinterpret_cast<uint8_t*>(r->d_lown + S), r->d_lown, nullptr, true,
-                            s);
+    // Destinations too many for a few launches' arguments are staged in pinned
+    // memory, so that the call does not wait for the work ahead on `s`, and
+    // apart from p->ldst(), which a captured ii_load_device_noalloc of as many
+    // reads again at replay. A captured load's go as arguments of as many
+    // launches as it takes: the graph keeps those.
+    const bool few = fits_by_value(p, true), staged = !few && !captured;
+    std::vector<uint64_t> copy;
+    uint64_t* words = p->ldst();
+    if (staged) {
+        if (!r->h_lown) {
+            II_HIP(host_alloc(&r->h_lown, p->lstage.size() * sizeof(uint64_t)));
+            std::copy(p->lstage.begin() + S, p->lstage.end(), r->h_lown + S);
+        }
+        if (r->lown_staged) II_HIP(hipEventSynchronize(r->lown_sent));
+        words = r->h_lown;
+    } else if (!few) {
+        try {
+            copy = p->lstage;
+        } catch (const std::bad_alloc&) {
+            return fail(II_ENOMEM, "destination rows: host allocation failed");
+        }
+        words = copy.data();
+    }
+    layout_dst(p, dst, words);
+    const int rc = put_rows(p, words, reinterpret_cast<uint8_t*>(r->d_lown + S), r->d_lown, nullptr,
+                            true, !staged, s);
     if (rc) return rc;
+    if (staged) {
+        II_HIP(hipEventRecord(r->lown_sent, s));
+        r->lown_staged = true;
+    }
     r->lown_ok = !captured;
     return II_OK;
 }

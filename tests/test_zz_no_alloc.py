@@ -132,6 +132,48 @@ def test_noalloc_table_sizes(orc, n):
     plan.free()
 
 
+@pytest.mark.parametrize("n", [40, 3000], ids=["rows-as-arguments", "rows-uploaded"])
+@pytest.mark.parametrize("gap", [0, 256], ids=["arena", "own"])
+def test_noalloc_captured_then_other_loads(orc, n, gap):
+    """A captured call goes to its own destinations at every replay, whatever
+    other loads of the plan did in between: ii_load_device and the call
+    itself into an arena, ii_load_device into destinations of their own."""
+    t = synth.stress(n=n, chunk=1 << 18)
+    plan = ii.ii_plan(t)
+    _, off = plan.tensors()
+    blob = synth.blob(t)
+    image = torch.from_numpy(blob).to(DEV)
+    tensors = orc.load(orc.nbytes(t), t.src_offset, blob)
+
+    def place(gap):
+        rel = off + np.arange(n, dtype=np.uint64) * np.uint64(gap)
+        buf = torch.full((int(rel[-1]) + tensors[-1].size + 2048,), 0xA5, dtype=torch.uint8,
+                         device=DEV)
+        want = np.full(buf.numel(), 0xA5, np.uint8)
+        for o, d in zip(tensors, rel):
+            want[1024 + int(d):1024 + int(d) + o.size] = o
+        return buf, np.uint64(buf.data_ptr() + 1024) + rel, want
+
+    captured, other, arena = place(gap), place(512), place(0)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        ii.ii_load_device_noalloc(plan, image, captured[1], torch.cuda.current_stream(DEV))
+    for k in range(4):
+        for buf, _, _ in (captured, other, arena):
+            buf.fill_(0xA5)
+        if k:
+            ii.ii_load_device(plan, image, other[1])
+            ii.ii_load_device(plan, image, arena[1])
+            ii.ii_load_device_noalloc(plan, image, arena[1])
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        for what, (buf, _, want) in zip(("captured", "other", "arena"), (captured, other, arena)):
+            if what == "captured" or k:
+                assert np.array_equal(buf.cpu().numpy(), want), (k, what)
+    plan.free()
+
+
 def test_noalloc_refuses_tables_beyond_the_workspace():
     """The Llama-70B-shaped plan needs 275 MB of tile tables: refused with
     II_ESCRATCH before anything is checked or enqueued."""
