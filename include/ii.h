@@ -149,12 +149,12 @@ void ii_plan_free(ii_plan_t* plan);
  * segments' bytes, packed, when it has gaps between segments), copy it to a
  * device slot with one hipMemcpyAsync, then scatter it into its tensors
  * with the device kernel. A pinned blob's chunk skips the host slot: it is
- * copied straight from the blob. A pinned blob whose table has gaps between
- * segments, or at most 16 chunks and few small scattered tensors, skips the
- * chunks altogether: one launch on `stream` reads the blob over the host
- * link, as ii_load_device does from pinned memory (a traced load runs the
- * chunks all the same, its chunks with gaps moved as ii_plan_copy_bytes
- * says).
+ * copied straight from the blob. Some tables (ii_plan_pinned_link) skip the
+ * chunks altogether when the blob is pinned: one launch on `stream` reads the
+ * blob over the host link, as ii_load_device does from pinned memory. It
+ * starts behind the work already on `stream`: no copy runs ahead of it. (A
+ * traced load runs the chunks all the same, its chunks with gaps moved as
+ * ii_plan_copy_bytes says.)
  * Chunks holding no segment are not touched. Chunk k's copy and scatter
  * run on lane k mod lanes (see ii_plan_set_ring), so with two or more lanes
  * chunk k+1's copy overlaps chunk k's scatter. A slot is
@@ -466,6 +466,14 @@ int ii_plan_tiles(const ii_plan_t* plan, uint32_t* tile_bytes, uint64_t* num_til
  * Errors: II_EINVAL (NULL plan). */
 int ii_plan_layout_tiles(const ii_plan_t* plan, uint64_t* num_tiles, uint32_t* seg_order,
                          uint32_t* first, uint32_t* last, uint32_t* window);
+/* 1 if an ii_load of this plan from a pinned blob (untraced, the device seeing
+ * the blob at its host address) is one launch that reads the blob over the
+ * host link, 0 if it runs the chunk pipeline: 1 when more than an eighth of the
+ * payload lies in chunks that the pipeline would move row by row (by 2-D
+ * copies, or gathered on the host), or when the payload is at most 32 MiB and
+ * the 128-byte lines that hold it come to at most 1.03 times
+ * ii_plan_copy_bytes and the two lines the span begins and ends in. Both write the same bytes. 0 for a NULL plan. */
+int ii_plan_pinned_link(const ii_plan_t* plan);
 /* which of its two variants the resident-image kernel runs for a table of
  * this shape: 1 for the variant for tables of many small tensors (tiles that
  * one segment meets take a path without LDS staging, and every tile issues

@@ -55,6 +55,10 @@ struct DstRange {
 // 117.4 and 118.9. Below 20 MB a load takes the host longer than the device.
 constexpr uint64_t kCacheBytes = 300ull << 20;
 
+// Largest payload of a dense table whose pinned blob is read over the link
+// (reads_over_link, runtime.hip, says why the line lies here).
+constexpr uint64_t kLinkBytes = 32ull << 20;
+
 // Static device workspace of ii_load_device_noalloc (runtime.hip): the
 // kernel's tables, and after them what the segments' rows are formed from
 // (28 bytes for each 32-byte row).
@@ -85,6 +89,9 @@ struct ii_plan_s {
     uint64_t payload = 0, arena_bytes = 0, max_align = 1;
     uint64_t lo = 0, hi = 0;
     uint64_t copy_bytes = 0;  // host-to-device bytes of a load from a pinned blob
+    // of those, the payload of chunks moved row by row: by 2-D copies or
+    // gathered on the host
+    uint64_t row_bytes = 0;
     uint64_t chunk_bytes = 0;
     size_t num_chunks = 0;
     std::vector<uint64_t> chunk_seg_begin;  // num_chunks + 1
@@ -154,6 +161,8 @@ struct ii_plan_s {
     bool layout_mixed = false;
     // whether an image load runs it for its size (see kCacheBytes)
     bool layout_cached = false;
+    // whether an untraced load reads a pinned blob over the link
+    bool pinned_link = false;
     // for the destination checks: the first non-empty tensor (n if none),
     // whether there are empty ones, the end of the last non-empty tensor in
     // the layout and the largest alignment of a non-empty one

@@ -351,6 +351,9 @@ extern "C" int ii_plan(const ii_tensor_desc* table, size_t n, uint64_t chunk_byt
             p->chunk_group_begin[k + 1] = p->groups.size();
             p->chunk_pinned[k] = how;
             p->copy_bytes += how == kPinnedInPlace ? e - b : p->chunk_plen[k];
+            bool rows = how == kPinnedGather;
+            for (size_t g = g0; g < p->groups.size(); ++g) rows |= p->groups[g].count > 1;
+            if (rows) p->row_bytes += p->chunk_plen[k];
         }
 
         // 6. ring tiles: per chunk, tile_bytes of segment bytes each (packed
@@ -450,6 +453,10 @@ extern "C" int ii_plan(const ii_tensor_desc* table, size_t n, uint64_t chunk_byt
             p->layout_mixed = pct <= 100 && (many * 100 >= (uint64_t)pct * G ||
                                              (two * 100 >= 3 * G && shifted * 2 >= bytes));
             p->layout_cached = pct <= 100 && bytes <= kCacheBytes;
+            // see reads_over_link (256: the span's first and last line)
+            p->pinned_link =
+                8 * p->row_bytes > bytes ||
+                (bytes <= kLinkBytes && 100 * p->line_bytes <= 103 * p->copy_bytes + 100 * 256);
         }
         p->na_ranges.reserve(n);
     } catch (const std::bad_alloc&) {
@@ -584,6 +591,8 @@ extern "C" int ii_plan_layout_tiles(const ii_plan_t* p, uint64_t* num_tiles, uin
     for (size_t g = 0; g < G && window; ++g) window[g] = (uint32_t)g;
     return II_OK;
 }
+
+extern "C" int ii_plan_pinned_link(const ii_plan_t* p) { return p && p->pinned_link ? 1 : 0; }
 
 extern "C" int ii_plan_layout_mixed(const ii_plan_t* p) { return p && p->layout_mixed ? 1 : 0; }
 

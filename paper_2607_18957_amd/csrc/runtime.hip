@@ -1052,35 +1052,39 @@ static int run_device(ii_plan_t* p, const uint8_t* image, const uint64_t* dst, h
 }
 
 // Whether a load from a pinned blob goes by one launch that reads the blob
-// over the link (scatter_layout_link) instead of the chunk pipeline:
-//   tables with gaps: the pipeline's 2-D copies of their rows hold the
-//     calling thread for the whole transfer, and its host gather copies short
-//     rows one by one (one rank of four of a 3.0 GB model, 749 MB: 13.6 ->
-//     13.04 ms; of smaller models in rows of 240, 482 and 964 bytes: 1060 ->
-//     624 us, 4.20 -> 2.33 and 5.09 -> 4.20 ms). The one kind measured that
+// over the link (scatter_layout_link) instead of the chunk pipeline. The
+// pipeline's first `depth` chunks are copied while the work ahead on the
+// caller's stream still runs; one launch starts behind it. So the launch is
+// taken only where the pipeline costs much by itself or has little to hide:
+//   tables with more than an eighth of their payload in chunks moved row by
+//     row: the pipeline's 2-D copies hold the calling thread while they run, its
+//     host gather copies short rows one by one. One rank of four of a 3.0 GB
+//     model, 749 MB, a quarter to two thirds of it in such chunks of 4, 16 and
+//     64 MiB: 15.4, 15.4 and 13.9 ms -> 13.05, the caller held for up to 12.7 ms
+//     -> 5 us; behind other work, from its end, 15.2, 13.7 and 11.2 ms -> 13.03.
+//     66 MB in rows of 2 KiB 1.53 -> 1.18 ms, behind other work 1.21 -> 1.17;
+//     31 MB in rows of 433 and 165 bytes 1000 -> 639 us. (Tables with smaller
+//     shares were not met; the line halves the least measured.) The kind that
 //     loses is a single chunk of some 10 MB loaded back to back from several
-//     plans, whose gather the pipeline hides behind the load before: 187 ->
-//     206 us (353 -> 218 when each load is waited for);
-//   others of at most kLinkChunks chunks: the pipeline's first copy and last
-//     scatter, its hand-overs and the copy engines' start-up are then a
-//     sizeable part (16.8 MB in 5 chunks: 378 -> 312 us with the host
-//     waiting, 707 -> 302 us in back-to-back loads; 200 MB in 13: 3.62 ->
-//     3.50 ms). With more chunks the two are within 1.3% (3.0 GB in 45:
-//     52.8 and 52.1 ms; 948 MB in 57, permuted: 16.9 both), and the copy
-//     engines, which prefetch before the caller's earlier work is done,
-//     stay the path. So they do where small tensors lie scattered: the link
-//     carries whole 128-byte lines, and where those come to more than 1.03
-//     times the payload the pipeline is level or ahead (tensors of 64-512
-//     bytes 133 and 105 us, 512-8192 bytes 1028 and 1012 us; of 528-33792
-//     bytes, lines 1.016 times the payload, 930 against 1005 us).
+//     plans, whose gather the pipeline hides behind the load before (187 -> 206
+//     us; 353 -> 218 when each is waited for);
+//   others of at most kLinkBytes: the pipeline's first copy and last scatter,
+//     its hand-overs and the copy engines' start-up are then a sizeable part
+//     (17 MB in 4 MiB chunks: 377 -> 312 us on an idle stream, 707 and more ->
+//     301 back to back; 31 MB: 663 -> 568 and 1395 -> 558), and the copies that
+//     run ahead save no more than the load's own time (behind other work 160
+//     and 434 us against 303 and 559). Larger ones gain 3 to 8% on an idle
+//     stream (82 MB 1569 -> 1447 us, 327 MB 5.89 -> 5.73 ms) and would lose up
+//     to depth * chunk_bytes of overlap behind other work (327 MB in 64 MiB
+//     chunks: 2.35 ms -> 5.70 ms). Where small tensors lie scattered the
+//     pipeline is ahead at any size: the link carries whole 128-byte lines, and
+//     where those come to more than 1.03 times what the pipeline copies (and the
+//     two at the span's ends, which weigh in tables of some 10 KB) it is
+//     level or slower (tensors of 64-512 bytes 133 and 105 us, 512-8192 bytes
+//     1028 and 1012 us; of 528-33792 bytes, lines 1.016 times the payload, 930
+//     against 1005 us).
 // A traced load always runs the pipeline whose timeline it records.
-constexpr size_t kLinkChunks = 16;
-
-static bool reads_over_link(const ii_plan_t* p) {
-    if (p->trace) return false;
-    if (p->packed_distinct) return true;
-    return p->num_chunks <= kLinkChunks && 100 * p->line_bytes <= 103 * p->payload;
-}
+static bool reads_over_link(const ii_plan_t* p) { return !p->trace && p->pinned_link; }
 
 static int run_pinned(ii_plan_t* p, const uint8_t* blob, const uint64_t* dst, hipStream_t stream) {
     const int rc = run_image(p, blob, dst, stream, 0, 0);

@@ -373,8 +373,8 @@ def test_pinned_blob_read_over_the_link(orc, tiles):
     """The kernel that reads pinned host memory: at most 256 workgroups that
     take four tiles at a time, around the sizes where a run is short, where
     every workgroup has exactly one run and where some take a second. The
-    load of a pinned blob in up to 16 chunks takes it, with 17 the chunk
-    pipeline runs; each also fixes the ring's configuration."""
+    load of a small pinned blob takes it however many chunks it has, and also
+    fixes the ring's configuration."""
     total = tiles * 4096 - 7
     sizes = [total // 3 + 1, 13, total - total // 3 - 14]
     t = oracle_pins._u8_table(sizes, [5 + sizes[1], 5, 5 + sizes[0] + sizes[1]], [1, 1, 1])
@@ -384,10 +384,62 @@ def test_pinned_blob_read_over_the_link(orc, tiles):
         t.chunk_bytes = max(16, -(-total // chunks) + 15 & ~15)
         for mode in ("pinned", "image-pinned"):
             plan = _load_arena(orc, t, mode=mode, blob=blob)
+            assert plan.pinned_link
             if mode == "pinned":
                 with pytest.raises(ii.IIError) as e:
                     plan.set_ring(2, 2, 2)
                 assert e.value.code == ii.EBUSY
+
+
+def _moves_by_copies(load, monkeypatch):
+    """Whether a load goes through the chunk pipeline: with the first copy
+    made to fail, that fails; a load over the link makes none."""
+    torch.cuda.synchronize()
+    monkeypatch.setenv("II_TEST_FAIL_AT", "h2d:1")
+    try:
+        load()
+        return False
+    except ii.IIError as e:
+        assert e.code == ii.EHIP
+        return True
+    finally:
+        monkeypatch.delenv("II_TEST_FAIL_AT")
+
+
+_ROUTES = {
+    "tiny": (lambda: synth.tiny(), True),
+    "tiny-shard": (lambda: synth.tiny_tp(1, 4), True),
+    "scattered": (lambda: synth.stress(n=3000, lo_bytes=64, hi_bytes=512), False),
+    "above-32M": (lambda: synth.transformer("m", 4, 512, 2048, 512, 8192, chunk=16 << 20), False),
+}
+
+
+@pytest.mark.parametrize("case", _ROUTES)
+def test_which_way_a_pinned_blob_goes(orc, monkeypatch, case):
+    """ii_load of a pinned blob runs what the plan's rule says: one launch
+    over the link, or the chunk pipeline, which a traced load always runs.
+    Both write the same bytes."""
+    make, link = _ROUTES[case]
+    t = make()
+    plan = _load_arena(orc, t, mode="pinned")
+    assert plan.pinned_link == link
+    hb = ii.ii_host_alloc(t.blob_bytes)
+    hb.numpy()[:] = synth.blob(t)
+    arena = torch.zeros(plan.arena_bytes, dtype=torch.uint8, device=DEV)
+    dst = arena.data_ptr() + plan.tensors()[1]
+    load = lambda: ii.ii_load(plan, hb, dst)  # noqa: E731
+    load()
+    assert _moves_by_copies(load, monkeypatch) == (not link)
+    if not link:
+        load()
+    plan.set_trace(True)
+    load()
+    assert plan.trace()["copy_start"].size == plan.num_chunks
+    assert _moves_by_copies(load, monkeypatch)
+    load()
+    torch.cuda.synchronize()
+    want = _expect_arena(orc, t, synth.blob(t), np.zeros(plan.arena_bytes, np.uint8))
+    assert np.array_equal(arena.cpu().numpy(), want)
 
 
 def test_pinned_shard_of_odd_rows(orc):
@@ -1354,6 +1406,7 @@ def test_injected_failure(orc, monkeypatch, site, nth, mode):
     if mode == "pinned":
         pinned = ii.ii_host_alloc(blob.size)
         pinned.numpy()[:] = blob
+        plan.set_trace(True)  # the chunk pipeline, not one launch over the link
     image = torch.from_numpy(blob).to(DEV) if mode in ("image", "noalloc") else None
     old = synth.transformer("tiny-old", 4, 256, 1024, 256, 8192, seed=31, chunk=1 << 20)
     po = ii.ii_plan(old)

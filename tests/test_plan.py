@@ -355,6 +355,46 @@ def _expected_copy_bytes(op, align=256, max_groups=2):
     return total
 
 
+def _expected_row_share(op, align=256, max_groups=2):
+    """Payload in chunks that the pipeline moves row by row, and the payload:
+    at most `max_groups` groups of runs of which one has several rows, or
+    gathered on the host (see _expected_copy_bytes)."""
+    rows = total = 0
+    ch, off, ln = op["seg_chunk"], op["seg_chunk_off"].astype(np.int64), op["seg_len"].astype(np.int64)
+    for k in np.unique(ch):
+        m = ch == k
+        runs, groups = _run_groups([int(x) for x in off[m]], [int(x) for x in ln[m]])
+        b = int(off[m].min()) // align * align
+        e = min(int(op["chunk_len"][k]), -(-int((off[m] + ln[m]).max()) // align) * align)
+        payload = int(ln[m].sum())
+        total += payload
+        if payload == int(op["chunk_len"][k]):
+            continue
+        if len(runs) > groups if groups <= max_groups else 4 * (e - b - payload) > e - b:
+            rows += payload
+    return rows, total
+
+
+def _expected_line_bytes(plan, s, lo, chunk):
+    """Bytes of the 128-byte source lines that hold the segments, taken in
+    layout order; a line that one segment ends in and the next starts in
+    counts once."""
+    order = plan.layout_tiles()["seg_order"].astype(np.int64)
+    src = lo + s["chunk"].astype(np.int64) * chunk + s["chunk_off"].astype(np.int64)
+    a = src[order] // 128
+    b = (src[order] + s["len"].astype(np.int64)[order] - 1) // 128
+    return 128 * (int((b - a + 1).sum()) - int((a[1:] == b[:-1]).sum()))
+
+
+def _expected_pinned_link(plan, op, s, chunk):
+    lo = int(plan.span[0])
+    rows, total = _expected_row_share(op)
+    if 8 * rows > total:
+        return True
+    return (total <= 32 << 20
+            and 100 * _expected_line_bytes(plan, s, lo, chunk) <= 103 * plan.copy_bytes + 25600)
+
+
 def _compare_rows(orc, table, chunk=None):
     chunk = chunk or table.chunk_bytes
     plan = ii.ii_plan(table, chunk)
@@ -379,6 +419,7 @@ def _compare_rows(orc, table, chunk=None):
     assert np.array_equal(s["len"].astype(np.uint64), op["seg_len"])
     assert sb[0] == 0 and sb[-1] == plan.num_segments
     assert plan.copy_bytes == _expected_copy_bytes(op)
+    assert plan.pinned_link == _expected_pinned_link(plan, op, s, chunk)
     _check_tiles(plan, s, l)
     _check_layout_tiles(plan, s)
     _check_packing(plan, s)
@@ -428,6 +469,51 @@ def test_pinned_copy_bytes_by_group_limit(orc, monkeypatch, groups_max):
                                np.asarray(t.src_row_stride, np.uint64), chunk)
             assert plan.copy_bytes == _expected_copy_bytes(op, max_groups=groups_max), chunk
             plan.free()
+
+
+def _gap_behind(t, tensors, gap=4096):
+    """t with a gap of `gap` bytes in the file behind its first `tensors`
+    tensors (in file order)."""
+    at = np.sort(np.asarray(t.src_offset))[tensors]
+    t.src_offset[t.src_offset >= at] += np.uint64(gap)
+    t.blob_bytes += gap
+    return t
+
+
+M = 1 << 20
+_LINK_CASES = {
+    # dense: by size, whatever the chunks
+    "dense-17M": (lambda: synth.tiny(), True),
+    "dense-17M-in-257-chunks": (lambda: synth.tiny(chunk=64 << 10), True),
+    "dense-at-the-limit": (lambda: oracle_pins._u8_table([31 * M, M], [0, 31 * M], [1, 1]), True),
+    "dense-above-it": (lambda: oracle_pins._u8_table([31 * M, M + 1], [0, 31 * M], [1, 1]), False),
+    "dense-3G-in-12-chunks":
+        (lambda: synth.transformer("m", 16, 2048, 8192, 512, 128256, chunk=256 * M), False),
+    # ... and by the source lines of small scattered tensors
+    "scattered": (lambda: synth.stress(n=3000, lo_bytes=64, hi_bytes=512, header=3), False),
+    "scattered-larger": (lambda: synth.stress(n=2000, lo_bytes=8192, hi_bytes=16384), True),
+    # one gap makes neither a sharded table
+    "scattered-one-gap":
+        (lambda: _gap_behind(synth.stress(n=3000, lo_bytes=64, hi_bytes=512), 1500), False),
+    "3G-one-gap": (lambda: _gap_behind(
+        synth.transformer("m", 16, 2048, 8192, 512, 128256, chunk=64 * M), 70), False),
+    "17M-one-gap": (lambda: _gap_behind(synth.tiny(), 10), True),
+    # shards: part of their payload lies in rows, whatever the size
+    **{f"shard-{c}M": (lambda c=c: synth.transformer_tp("m", 16, 2048, 8192, 512, 128256, 1, 4,
+                                                        chunk=c * M), True) for c in (4, 16, 64)},
+}
+
+
+@pytest.mark.parametrize("case", _LINK_CASES)
+def test_which_pinned_blobs_are_read_over_the_link(case):
+    make, want = _LINK_CASES[case]
+    t = make()
+    plan = ii.ii_plan(t, getattr(t, "chunk_bytes", 0) or 4 * M)
+    s, (_, chunk_len, _) = plan.segments(), plan.chunks()
+    op = dict(seg_chunk=s["chunk"], seg_chunk_off=s["chunk_off"], seg_len=s["len"],
+              chunk_len=chunk_len)
+    assert plan.pinned_link == want
+    assert plan.pinned_link == _expected_pinned_link(plan, op, s, plan.chunk_bytes)
 
 
 def test_tp_shard_llama8b(orc):
