@@ -236,9 +236,11 @@ int ii_load_file(ii_plan_t* plan, int fd, uint64_t file_bytes, void* const* dst_
  *                address, as hipHostMalloc and ii_host_alloc give it (checked,
  *                II_EINVAL). From pinned host memory the kernel reads the blob over the host link
  *                itself: no ring and no copy engine, one launch of at most
- *                256 workgroups that walk the windows in order -- the
- *                lowest latency for small loads, and the link's rate for
- *                large ones.
+ *                256 workgroups (64 for most tables of 64 MiB and more) that
+ *                walk the windows in order -- the lowest latency for small
+ *                loads, and the link's rate for large ones. Kernels on other
+ *                streams run slower meanwhile, which the copy engines spare
+ *                them.
  *   image_bytes  size of the image; must be >= the plan's span end hi.
  *   dst_ptrs     as for ii_load; must not overlap [dev_image, +hi).
  *   stream       the kernel runs on this stream, after the work already on

@@ -354,7 +354,7 @@ static LayoutTable layout_table(const ii_plan_t* p, uint8_t* at, const LayoutBlo
                                 const LayoutSeg* rows) {
     return LayoutTable{reinterpret_cast<const TileDev*>(at + l.tiles),
                        p->lwin.empty() ? nullptr : reinterpret_cast<const uint32_t*>(at + l.win),
-                       p->nltiles, rows};
+                       p->nltiles, rows, p->lseg.size()};
 }
 
 // Segments whose rows one launch forms from its arguments, and whether a

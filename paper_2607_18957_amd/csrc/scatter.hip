@@ -79,8 +79,7 @@ static_assert((1ull << 32) / 1024 <= kMaxGridBlocks, "a chunk's tiles fit one la
 
 namespace {
 
-constexpr uint32_t kLinkBlocks = 256;  // workgroups of scatter_layout_link
-constexpr uint32_t kLinkRun = 4;       // consecutive tiles one of them takes at a time
+constexpr uint32_t kLinkRun = 4;  // consecutive tiles a link workgroup takes at a time
 
 // Global-address-space accesses: plain pointers made from integer addresses
 // would be generic (flat) accesses, which also count against the LDS wait
@@ -323,12 +322,16 @@ __global__ __launch_bounds__(kBlock) void scatter_layout(
 // many reads are in flight decides how close it gets. With one workgroup per
 // tile the whole chip's worth of reads queues at the link at once, in an
 // order that spreads over 33 MB of the blob: a launch then costs ~55 us on
-// top of its bytes (16.8 MB in 354 us, 3.0 GB at 55.6 GB/s). kLinkBlocks
-// workgroups (one per compute unit, two wavefronts each) that walk the tiles
-// front to back keep ~1 MB in flight and read a compact moving window: 16.8
-// MB in 302 us, 3.0 GB at 57.5 GB/s, and the rest of each compute unit stays
-// free for other kernels. Swept from 32 to 512 workgroups: 192 and more are
-// level, 64 too, 96 to 144 lose 4-7%, 32 loses 20%.
+// top of its bytes (16.8 MB in 354 us, 3.0 GB at 55.6 GB/s). 256 workgroups
+// (one per compute unit, two wavefronts each) that walk the tiles front to
+// back keep ~1 MB in flight and read a compact moving window: 16.8 MB in 302
+// us, 3.0 GB at 57.5 GB/s. Swept from 32 to 512 workgroups: 192 and more are
+// level, 64 nearly, 96 to 144 lose 4-7%, 32 loses 20%.
+//   Other kernels run slower meanwhile, for as long as the load takes: beside
+// 256 workgroups bf16 products of 4096 x 4096 matrices took 1.9 to 5 times
+// as long, beside 64 of them 1.5 to 1.6 times. So large tables go with 64
+// (link_blocks): a 749 MB shard 13.05 -> 13.08 ms alone and 13.6 -> 13.4 beside
+// those products, 948 MB of permuted tensors 16.95 -> 17.04 ms.
 //   Each workgroup takes kLinkRun consecutive tiles at a time: where source
 // and destination are not congruent, neighbouring tiles share a 128-byte
 // source line, and the one L2 that both now go through fetches it over the
@@ -342,7 +345,7 @@ __global__ __launch_bounds__(kBlock) void scatter_layout_link(
     const uint32_t* __restrict__ win, const LayoutSeg* __restrict__ segs, uint64_t base,
     uint32_t tile_bytes, uint32_t ntiles) {
     const uint64_t sb = reinterpret_cast<uint64_t>(span);
-    // ntiles < 2^31 and a step is at most kLinkBlocks * kLinkRun: no wrap
+    // ntiles < 2^31 and a step is at most 256 * kLinkRun: no wrap
     for (uint32_t g0 = blockIdx.x * kLinkRun; g0 < ntiles; g0 += gridDim.x * kLinkRun) {
         const uint32_t g1 = min(ntiles, g0 + kLinkRun);
         for (uint32_t g = g0; g < g1; ++g) {
@@ -546,7 +549,7 @@ hipError_t launch_scatter_layout(const uint8_t* span, const LayoutTable& t, uint
                            t.tiles, t.win, t.rows, base, tile_bytes, n);
         break;
     case ImageKernel::kLink:
-        gx = std::min((n + kLinkRun - 1) / kLinkRun, kLinkBlocks);
+        gx = std::min((n + kLinkRun - 1) / kLinkRun, link_blocks(n, t.nrows));
         hipLaunchKernelGGL(scatter_layout_link, dim3(gx), dim3(kBlock), 0, stream, span, t.tiles,
                            t.win, t.rows, base, tile_bytes, n);
         break;

@@ -15,6 +15,7 @@ struct LayoutTable {
     const uint32_t* win;  // null: tile g is window g
     uint64_t ntiles;
     const LayoutSeg* rows;
+    uint64_t nrows;
 };
 
 enum class ImageKernel { kDense, kMixed, kLink };

@@ -37,6 +37,18 @@ II_HD void grid_shape(uint64_t n, uint32_t* gx, uint32_t* gy) {
     *gx = (uint32_t)(n ? (n + y - 1) / y : 1);
 }
 
+// Workgroups of scatter_layout_link (its comment has the reasons): a quarter
+// of the chip for tables of 64 MiB and more in 4 KiB tiles. Smaller ones take
+// all of it, since 64 workgroups need longer to fill the link (17 MB 312 ->
+// 333 us, 31 MB 568 -> 583, 66 MB 1176 -> 1180, 82 MB level), and so do tables
+// of more segments than tiles, whose workgroups spend longer forming rows
+// (86 MB in pieces of 64-512 bytes 2.63 -> 2.90 ms, 166 MB in pieces of
+// 512-8192 bytes 3.09 -> 3.12, 948 MB in pieces of 64 bytes to 64 KiB, 0.43 a
+// tile, 0.5%).
+II_HD uint32_t link_blocks(uint64_t ntiles, uint64_t nrows) {
+    return ntiles >= 16384 && nrows <= ntiles ? 64 : 256;
+}
+
 // The layout tiles one segment takes part in, for layouts whose windows all
 // hold segment bytes (tile m is window m): the segment meets tiles [m0, m1];
 // it is the first of tile m0 if the segment before it ends in an earlier

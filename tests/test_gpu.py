@@ -391,6 +391,22 @@ def test_pinned_blob_read_over_the_link(orc, tiles):
                 assert e.value.code == ii.EBUSY
 
 
+@pytest.mark.parametrize("tiles,small", [(16383, 0), (16384, 0), (16385, 0), (16600, 0),
+                                         (16384, 16382), (16384, 16384)])
+def test_large_pinned_image_over_the_link(orc, tiles, small):
+    """Around the size from which fewer workgroups read the link (16,384
+    tiles), and around as many segments as tiles, which takes all of them
+    again: `small` tensors of 700 bytes ahead of two that fill the rest."""
+    total = tiles * 4096 - 7
+    sizes = [700] * small + [total - 700 * small - 5000, 5000]
+    assert len(sizes) == small + 2
+    off = np.cumsum([3] + sizes[::-1][:-1])[::-1]      # the file in reverse order
+    t = oracle_pins._u8_table(sizes, [int(x) for x in off], [1] * len(sizes))
+    t.name, t.chunk_bytes = f"{tiles} tiles, {small + 2} segments", 256 << 20
+    plan = _load_arena(orc, t, mode="image-pinned", blob=synth.blob(3 + total, seed=tiles))
+    assert plan.layout_tiles()["first"].size == tiles and plan.num_segments == small + 2
+
+
 def _moves_by_copies(load, monkeypatch):
     """Whether a load goes through the chunk pipeline: with the first copy
     made to fail, that fails; a load over the link makes none."""
