@@ -168,7 +168,10 @@ void ii_plan_free(ii_plan_t* plan);
  *               ii_plan_set_ring) plus the plan's device tables; they are
  *               kept for later loads until ii_plan_release / ii_plan_free.
  *               A load that reads a pinned blob over the link allocates
- *               its kernel's tables instead of the ring.
+ *               its kernel's tables instead of the ring. The load that
+ *               first uploads or forms a plan's tables waits for that on the
+ *               null stream, and so for the work ahead of it there; after
+ *               ii_plan_prepare no load of a host blob does.
  *   host_blob   host address of blob byte 0. Pageable or pinned. Pageable
  *               blobs are read only during the call; a pinned blob
  *               (hipHostMalloc / ii_host_alloc) is read by DMA after the call
@@ -366,9 +369,11 @@ int ii_check_dst(const ii_plan_t* plan, void* const* dst_ptrs);
  * ii_plan_prepare -- allocate, on the current device, what the plan's loads
  * would otherwise allocate on first use: the staging ring (pinned host slots,
  * touched page by page so the first load does not fault them in; device
- * slots; streams; host copy threads) and the ring's device tables (the
- * resident-image kernel's tables are allocated and formed by the first load
- * that needs them). Optional:
+ * slots; streams; host copy threads) and the ring's device tables; where a
+ * load from a pinned blob reads it over the link (ii_plan_pinned_link), also
+ * the resident-image kernel's tables and rows, which such a load takes
+ * instead. (Other plans' first ii_load_device allocates and forms those.)
+ * Optional:
  * a cold-starting process can call it while other initialisation runs, so
  * the first load starts moving bytes at once (Sec. 4.2 overlaps independent
  * steps of the cold start). Idempotent. Errors: II_EINVAL (NULL plan, or a

@@ -678,6 +678,19 @@ static bool capturing(hipStream_t s) {
     return st != hipStreamCaptureStatusNone;
 }
 
+// Allocate the rows of destinations that are not one arena, and the pinned
+// staging for them if `staged`.
+static int ensure_own_rows(ii_plan_t* p, bool staged) {
+    Runtime* r = p->rt;
+    const size_t S = p->lseg.size();
+    if (S && !r->d_lown) II_HIP(dev_alloc(&r->d_lown, S * (sizeof(LayoutSeg) + 28)));
+    if (S && staged && !r->h_lown) {
+        II_HIP(host_alloc(&r->h_lown, p->lstage.size() * sizeof(uint64_t)));
+        std::copy(p->lstage.begin() + S, p->lstage.end(), r->h_lown + S);
+    }
+    return II_OK;
+}
+
 // Make d_lown hold destinations that are not one arena for the work enqueued
 // next on `s`: ordered after the work that formed or read its rows, on
 // whichever stream (a wait for an event of the same stream does nothing).
@@ -686,8 +699,9 @@ static bool capturing(hipStream_t s) {
 // the streams outside it.
 static int image_own_rows(ii_plan_t* p, const uint64_t* dst, hipStream_t s, bool captured) {
     Runtime* r = p->rt;
-    const size_t S = p->seg_len.size();
-    if (!r->d_lown) II_HIP(dev_alloc(&r->d_lown, S * (sizeof(LayoutSeg) + 28)));
+    const bool few = fits_by_value(p, true), staged = !few && !captured;
+    int rc = ensure_own_rows(p, staged);
+    if (rc) return rc;
     if (r->lown_used && !captured) II_HIP(hipStreamWaitEvent(s, r->lown_idle, 0));
     if (r->lown_ok) return II_OK;
     // Destinations too many for a few launches' arguments are staged in pinned
@@ -695,14 +709,9 @@ static int image_own_rows(ii_plan_t* p, const uint64_t* dst, hipStream_t s, bool
     // apart from p->ldst(), which a captured ii_load_device_noalloc of as many
     // reads again at replay. A captured load's go as arguments of as many
     // launches as it takes: the graph keeps those.
-    const bool few = fits_by_value(p, true), staged = !few && !captured;
     std::vector<uint64_t> copy;
     uint64_t* words = p->ldst();
     if (staged) {
-        if (!r->h_lown) {
-            II_HIP(host_alloc(&r->h_lown, p->lstage.size() * sizeof(uint64_t)));
-            std::copy(p->lstage.begin() + S, p->lstage.end(), r->h_lown + S);
-        }
         if (r->lown_staged) II_HIP(hipEventSynchronize(r->lown_sent));
         words = r->h_lown;
     } else if (!few) {
@@ -714,8 +723,8 @@ static int image_own_rows(ii_plan_t* p, const uint64_t* dst, hipStream_t s, bool
         words = copy.data();
     }
     layout_dst(p, dst, words);
-    const int rc = put_rows(p, words, reinterpret_cast<uint8_t*>(r->d_lown + S), r->d_lown, nullptr,
-                            true, !staged, s);
+    rc = put_rows(p, words, reinterpret_cast<uint8_t*>(r->d_lown + p->lseg.size()), r->d_lown,
+                  nullptr, true, !staged, s);
     if (rc) return rc;
     if (staged) {
         II_HIP(hipEventRecord(r->lown_sent, s));
@@ -1467,7 +1476,12 @@ extern "C" int ii_plan_prepare(ii_plan_t* p) {
     if (rc) return rc;
     rc = ensure_ring_tables(p);
     if (rc) return rc;
-    return ensure_ring(p);
+    rc = ensure_ring(p);
+    if (rc || !p->pinned_link) return rc;
+    // a load from a pinned blob takes none of these but the image kernel's
+    // tables, and rows where the destinations are not one arena
+    rc = ensure_layout_tables(p);
+    return rc ? rc : ensure_own_rows(p, !fits_by_value(p, true));
 }
 
 extern "C" int ii_plan_release(ii_plan_t* p) {

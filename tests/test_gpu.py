@@ -1070,6 +1070,46 @@ def test_prepare_then_load(orc):
     _load_arena(orc, t, plan=plan)
 
 
+@pytest.mark.parametrize("dest", ["arena", "own"])
+@pytest.mark.parametrize("n", [40, 3000], ids=["few-tensors", "many-tensors"])
+def test_prepared_pinned_load_enqueues_and_returns(orc, n, dest):
+    """The first load of a prepared plan from a pinned blob, on the null
+    stream behind other work: it returns before that work is done (the plan's
+    tables are there, nothing is waited for), and writes after it."""
+    sizes = [5000 + 7 * (i % 3) for i in range(n)]
+    t = oracle_pins._u8_table(sizes, [int(x) for x in np.cumsum([0] + sizes[:-1])], [16] * n)
+    t.name, t.chunk_bytes = f"{n} tensors", 1 << 22
+    blob = synth.blob(sum(sizes), seed=n)
+    plan = ii.ii_plan(t)
+    assert plan.pinned_link
+    plan.prepare()
+    nb, off = plan.tensors()
+    gap = 4096 if dest == "own" else 0
+    at = off + np.arange(n, dtype=np.uint64) * np.uint64(gap)
+    buf, can = _canary_buffer(int(at[-1] + nb[-1]) + GUARD)
+    before = torch.empty_like(buf)
+    hb = ii.ii_host_alloc(blob.size)
+    hb.numpy()[:] = blob
+    a = torch.ones(4096, 4096, dtype=torch.float32, device=DEV) / 4096.0
+    a @ a
+    torch.cuda.synchronize()
+    for _ in range(100):
+        a = a @ a
+    before.copy_(buf)
+    pending = torch.cuda.Event()
+    pending.record()
+    ii.ii_load(plan, hb, buf.data_ptr() + at)      # the null stream, torch's current one
+    returned_early = not pending.query()
+    torch.cuda.synchronize()
+    want = can.copy()
+    for i in range(n):
+        o, b = int(at[i]), int(t.src_offset[i])
+        want[o:o + sizes[i]] = blob[b:b + sizes[i]]
+    assert np.array_equal(before.cpu().numpy(), can)
+    assert np.array_equal(buf.cpu().numpy(), want)
+    assert returned_early, "the load waited for the work ahead of it"
+
+
 def test_layout_windows_of_padding_only(orc):
     """Windows of the layout that hold only padding get no tile, so the image
     kernel reads a window index per tile; every mode, against the oracle."""
