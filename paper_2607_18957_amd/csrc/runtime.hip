@@ -369,17 +369,14 @@ static bool fits_by_value(const ii_plan_t* p, bool own_dst) {
 // own_dst destinations, LayoutRows and lengths, else LayoutRows and lengths
 // of rows that serve any arena. It goes as arguments of launches where by_value
 // says so and else into `stage` by one copy; of a pageable source that
-// returns once its bytes are staged. For failure injection rows and lengths
-// are an upload each, whichever way they go.
+// returns once its bytes are staged.
 static int put_rows(const ii_plan_t* p, const uint64_t* words, uint8_t* stage, LayoutSeg* rows,
                     TileDev* tiles, bool own_dst, bool by_value, hipStream_t s) {
     const uint32_t S = (uint32_t)p->lseg.size();
     const LayoutRow* lrows = p->lrows();
     const uint32_t* llen = p->llen();
-    II_HIP(injected(kSiteH2D) ? hipErrorUnknown : hipSuccess);
     if (by_value) {
         const uint32_t most = by_value_most(own_dst);
-        II_HIP(injected(kSiteH2D) ? hipErrorUnknown : hipSuccess);
         for (uint32_t j = 0; j < S; j += most) {
             const uint32_t n = std::min(most, S - j);
             LayoutArgs args;

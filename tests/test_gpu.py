@@ -1435,9 +1435,10 @@ _INJECT_CASES = [
     ("dev_alloc", 1, "pageable"), ("dev_alloc", 4, "pageable"),
     ("h2d", 1, "pageable"), ("h2d", 8, "pageable"), ("h2d", 8, "pinned"),
     ("launch", 1, "pageable"), ("launch", 9, "pageable"), ("launch", 5, "pinned"),
-    ("h2d", 1, "image"), ("launch", 1, "image"),
+    ("h2d", 1, "image"), ("launch", 1, "image"), ("launch", 2, "image"),
+    ("h2d", 1, "image-own"), ("launch", 1, "image-own"), ("launch", 2, "image-own"),
     ("launch", 1, "switch"), ("launch", 4, "switch"), ("h2d", 6, "switch"),
-    ("h2d", 2, "noalloc"), ("launch", 1, "noalloc"),
+    ("h2d", 1, "noalloc"), ("launch", 1, "noalloc"), ("launch", 2, "noalloc"),
     ("h2d", 3, "pertensor"),
 ]
 
@@ -1447,23 +1448,35 @@ _INJECT_CASES = [
 def test_injected_failure(orc, monkeypatch, site, nth, mode):
     """A HIP call made to fail part-way through a load (allocations on a
     fresh plan, a chunk copy or a scatter launch in the middle of the ring,
-    the scrub of a switch): the call returns II_ENOMEM or II_EHIP, nothing
+    the scrub of a switch; the upload of the image kernel's tables, of a table
+    too large to go as kernel arguments, the launch that forms them and the
+    kernel's): the call returns II_ENOMEM or II_EHIP, nothing
     touches the destination after it returned, the guard bands are intact,
     and the next call on the same plan is bit-exact."""
     t = synth.tiny(chunk=1 << 20)                  # 17 chunks
+    if site == "h2d" and mode in ("image", "image-own", "noalloc"):
+        t = synth.stress(n=1500, lo_bytes=64, hi_bytes=4096)
     plan = ii.ii_plan(t)
     plan.set_ring(3, 2, 2)
     _, off = plan.tensors()
     blob = synth.blob(t)
     buf, can = _canary_buffer(plan.arena_bytes + 2 * GUARD)
     base = buf.data_ptr() + GUARD
+    own = None  # the last tensor in memory of its own: destinations that are not one arena
+    if mode == "image-own":
+        own = torch.full((int(plan.tensors()[0][-1]),), 0xA5, dtype=torch.uint8, device=DEV)
+        scratch = torch.zeros(plan.arena_bytes, dtype=torch.uint8, device=DEV)
     s = torch.cuda.current_stream(DEV)
     pinned = None
     if mode == "pinned":
         pinned = ii.ii_host_alloc(blob.size)
         pinned.numpy()[:] = blob
         plan.set_trace(True)  # the chunk pipeline, not one launch over the link
-    image = torch.from_numpy(blob).to(DEV) if mode in ("image", "noalloc") else None
+    image = torch.from_numpy(blob).to(DEV) if mode in ("image", "image-own", "noalloc") else None
+    if own is not None:
+        dst = base + off
+        dst[-1] = own.data_ptr()
+        ii.ii_load_device(plan, image, scratch.data_ptr() + off, s)  # forms the plan's tables
     old = synth.transformer("tiny-old", 4, 256, 1024, 256, 8192, seed=31, chunk=1 << 20)
     po = ii.ii_plan(old)
     blob_old = synth.blob(old)
@@ -1475,6 +1488,8 @@ def test_injected_failure(orc, monkeypatch, site, nth, mode):
             ii.ii_load(plan, pinned, base + off, s)
         elif mode == "image":
             ii.ii_load_device(plan, image, base + off, s)
+        elif mode == "image-own":
+            ii.ii_load_device(plan, image, dst, s)
         elif mode == "noalloc":
             ii.ii_load_device_noalloc(plan, image, base + off, s)
         elif mode == "pertensor":
@@ -1493,6 +1508,10 @@ def test_injected_failure(orc, monkeypatch, site, nth, mode):
         want = can.copy()
         orc.arena(orc.nbytes(t), t.src_offset, t.dst_align, blob,
                   want[GUARD:GUARD + plan.arena_bytes])
+        if own is not None:
+            last = int(off[-1]), int(off[-1]) + own.numel()
+            own_want = want[GUARD + last[0]:GUARD + last[1]].copy()
+            want[GUARD + last[0]:GUARD + last[1]] = can[GUARD + last[0]:GUARD + last[1]]
     monkeypatch.setenv("II_TEST_FAIL_AT", f"{site}:{nth}")
     with pytest.raises(ii.IIError) as e:
         call()
@@ -1511,6 +1530,8 @@ def test_injected_failure(orc, monkeypatch, site, nth, mode):
         bad = np.flatnonzero(got != want)
         raise AssertionError(f"after the injected failure: {bad.size} bytes differ, first at "
                              f"{int(bad[0]) - GUARD}")
+    if own is not None:
+        assert np.array_equal(own.cpu().numpy(), own_want)
     _say(f"{mode}: {site} #{nth} failed with {e.value.name}; next call bit-exact")
     if pinned is not None:
         pinned.free()
