@@ -61,7 +61,9 @@ def _expect_arena(orc, table, blob, canary_slice):
 def _load_arena(orc, table, *, mode="pageable", depth=None, threads=None, blob=None,
                 stream=None, chunk=None, copy_streams=2, plan=None):
     """Load `table` into a canary-filled arena (plan layout) and compare the
-    whole buffer, guard bands included, with the oracle."""
+    whole buffer, guard bands included, with the oracle. Pinned blobs of many
+    tables are read over the link; mode "...-ring" sends them through the
+    chunk pipeline (a traced load) and checks by its timeline that it ran."""
     if plan is None:
         plan = ii.ii_plan(table, chunk or table.chunk_bytes)
         if depth:
@@ -79,6 +81,10 @@ def _load_arena(orc, table, *, mode="pageable", depth=None, threads=None, blob=N
     _say(f"[{table.name}] mode={mode} N={table.n} K={plan.num_chunks} S={plan.num_segments} "
          f"depth={depth} arena={plan.arena_bytes}")
     s = stream or torch.cuda.current_stream(DEV)
+    ring = mode.endswith("-ring")
+    if ring:
+        mode = mode[:-len("-ring")]
+        plan.set_trace(True)
     if mode == "pageable":
         ii.ii_load(plan, blob, base + off, s)
     elif mode == "pinned":
@@ -118,6 +124,11 @@ def _load_arena(orc, table, *, mode="pageable", depth=None, threads=None, blob=N
         hb.numpy()[:] = blob
         ii.ii_load_pertensor(plan, hb, base + off, s)
     s.synchronize()
+    if ring and plan.num_segments:
+        moved = np.unique(plan.segments()["chunk"])
+        assert np.isfinite(plan.trace()["copy_start"][moved]).all()
+    if ring:
+        plan.set_trace(False)
     got = buf.cpu().numpy()
     want = can.copy()
     want[lead:lead + plan.arena_bytes] = _expect_arena(orc, table, blob,
@@ -251,7 +262,7 @@ def test_image_more_tiles_than_one_dispatch(orc, monkeypatch):
     _say("many tiles: bit-exact")
 
 
-@pytest.mark.parametrize("mode", ["pageable", "pinned", "image", "image-pinned"])
+@pytest.mark.parametrize("mode", ["pageable", "pinned", "pinned-ring", "image", "image-pinned"])
 def test_tiny(orc, mode):
     _load_arena(orc, synth.tiny(), mode=mode)
 
@@ -276,7 +287,7 @@ def test_ring_depths_small_chunks(orc, depth, copy_streams):
     """4 KiB chunks: hundreds of slot reuses per load."""
     t = synth.stress(n=3000, chunk=4096, dst_align=16)
     _load_arena(orc, t, depth=depth, threads=2, copy_streams=copy_streams)
-    _load_arena(orc, t, mode="pinned", depth=depth, threads=2, copy_streams=copy_streams)
+    _load_arena(orc, t, mode="pinned-ring", depth=depth, threads=2, copy_streams=copy_streams)
 
 
 @pytest.mark.parametrize("mode", ["pertensor", "pertensor-pinned"])
@@ -532,7 +543,8 @@ def test_arenas_and_own_destinations_in_turn(orc, dst_align):
     """One plan loaded into arenas (rows of the plan's layout and a base) and
     into destinations of their own (resolved rows), in turn, through the ring
     and the image kernels, on two streams: no load may see another's rows.
-    The table has empty tensors, whose pointers are NULL."""
+    Rows of its own are formed by ii_load_device on one stream (k = 2), then on
+    the other (8), over the former ones. The table has empty tensors, whose pointers are NULL."""
     rng = np.random.default_rng(dst_align)
     sizes = [int(x) for x in rng.integers(0, 9000, 300)]
     sizes[0] = sizes[7] = sizes[-1] = 0
@@ -554,7 +566,7 @@ def test_arenas_and_own_destinations_in_turn(orc, dst_align):
         todo.append((blob, image, rel, arena, dst))
     torch.cuda.synchronize()
     for k, (blob, image, rel, arena, dst) in enumerate(todo):
-        s = streams[(k // 4) % 2]
+        s = streams[(k // 4) % 2 if k != 8 else 1]
         if k % 4 == 1:
             ii.ii_load(plan, blob, dst, s)
         elif k % 4 == 3:
@@ -692,7 +704,7 @@ def test_ring_handover_between_lanes(orc, depth, lanes):
     plan = ii.ii_plan(t)
     plan.set_ring(depth, 2, lanes)
     assert plan.num_chunks == 12
-    for mode in ("pinned", "pageable", "pinned", "pageable"):
+    for mode in ("pinned-ring", "pageable", "pinned-ring", "pageable"):
         _load_arena(orc, t, mode=mode, blob=t.blob, plan=plan)
 
 
@@ -935,8 +947,8 @@ def test_switch_llama8b_to_mistral7b(orc):
 
 # -- tensor-parallel shards: tables given as rows ------------------------------
 
-@pytest.mark.parametrize("mode", ["pageable", "pinned", "image", "image-pinned", "pertensor",
-                                  "pertensor-pinned"])
+@pytest.mark.parametrize("mode", ["pageable", "pinned", "pinned-ring", "image", "image-pinned",
+                                  "pertensor", "pertensor-pinned"])
 def test_tp_shards_tiny(orc, mode):
     """Every rank's shard of the unsharded tiny file, in every load mode:
     column blocks of the row-parallel weights arrive one segment per row,
@@ -947,7 +959,7 @@ def test_tp_shards_tiny(orc, mode):
             t = synth.tiny_tp(rank, size)
             _load_arena(orc, t, mode=mode)
             plan = _load_arena(orc, t, mode=mode, chunk=64 << 10, depth=2, threads=2)
-            if mode in ("pageable", "pinned") and size > 1:
+            if mode in ("pageable", "pinned", "pinned-ring") and size > 1:
                 lo, hi = plan.span
                 assert plan.copy_bytes < hi - lo
 
@@ -1045,10 +1057,11 @@ def test_tp_shard_llama8b_full(orc):
 def test_blob_pinned_over_its_span_only(orc, make):
     """A load reads only the blob's span [lo, hi): a blob pinned over that
     span alone (its header bytes outside any pinned allocation) takes the
-    pinned path and gives the same bytes."""
+    pinned paths and gives the same bytes."""
     t = make()
     assert t.src_offset.min() > 0
     _load_arena(orc, t, mode="pinned-span", depth=2, threads=2)
+    _load_arena(orc, t, mode="pinned-span-ring", depth=2, threads=2)
 
 
 def test_prepare_then_load(orc):
@@ -1317,13 +1330,43 @@ def test_pinned_group_copies_any_count(orc, monkeypatch):
     per chunk, into the same packed slot layout the host gather makes."""
     monkeypatch.setenv("II_PINNED_GROUPS_MAX", "64")
     for case, t, depth, cs in random_tables.cases(2026, 150):
-        for mode in ("pinned", "pinned-span"):
+        for mode in ("pinned-ring", "pinned-span-ring"):
             plan = ii.ii_plan(t)
             plan.set_ring(depth, 2, cs)
             _load_arena(orc, t, mode=mode, blob=t.blob, plan=plan)
             plan.free()
     for t in (synth.tiny_tp(1, 4, chunk=65552), synth.tiny_tp(3, 8, chunk=1 << 16)):
-        _load_arena(orc, t, mode="pinned")
+        _load_arena(orc, t, mode="pinned-ring")
+
+
+@pytest.mark.parametrize("how", ["words-2d", "odd-rows", "in-place"])
+def test_pinned_chunks_with_gaps_through_the_ring(orc, how):
+    """The three ways a pinned blob's chunk with gaps is moved: one 2-D copy
+    per column block whose rows are whole words; gathered on the host where
+    they are not; in place, gaps included, where its runs form more than two
+    groups and under a quarter of it is gaps -- the case whose tiles take the
+    windows of chunk offsets formed on the device."""
+    rng = np.random.default_rng(17)
+    if how == "in-place":
+        sizes = [int(x) for x in rng.integers(300, 9000, 600)]
+        gaps = [int(x) for x in rng.integers(1, 200, 600)]
+        src = [int(x) for x in np.cumsum([5] + [a + b for a, b in zip(sizes, gaps)][:-1])]
+        t = oracle_pins._u8_table(sizes, src, [1] * 600)
+    else:
+        width, row, rows = (512, 2048, 3000) if how == "words-2d" else (333, 1331, 3000)
+        t = oracle_pins._T([1], [(rows, width)], [width], [16])
+        t.src_row_stride = np.array([row], np.uint64)
+        src, sizes = [width], [rows * row]
+    t.name, t.names = how, [f"t{i}" for i in range(len(t.shapes))]
+    blob = synth.blob(src[-1] + sizes[-1], seed=3)
+    for chunk in (1 << 16, 1 << 20, 64 << 20):
+        t.chunk_bytes = chunk
+        plan = ii.ii_plan(t)
+        assert (plan.copy_bytes > plan.payload_bytes) == (how == "in-place")
+        plan.set_ring(3, 2, 2)
+        for _ in range(2):
+            _load_arena(orc, t, mode="pinned-ring", blob=blob, plan=plan)
+        plan.free()
 
 
 def test_random_tables_every_mode(orc):
@@ -1336,8 +1379,8 @@ def test_random_tables_every_mode(orc):
     for case, t, depth, cs in random_tables.cases(2026, count):
         if case % 50 == 0:
             _say(f"random table {case}: N={t.n} chunk={t.chunk_bytes} depth={depth} streams={cs}")
-        for mode in ("pageable", "pinned", "image", "image-pinned", "pertensor",
-                     "pertensor-pinned", "pinned-span", "file"):
+        for mode in ("pageable", "pinned", "pinned-ring", "image", "image-pinned", "pertensor",
+                     "pertensor-pinned", "pinned-span", "pinned-span-ring", "file"):
             plan = ii.ii_plan(t)
             plan.set_ring(depth, 2, cs)
             _load_arena(orc, t, mode=mode, blob=t.blob, plan=plan)
