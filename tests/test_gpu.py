@@ -656,8 +656,9 @@ def test_ring_race_stress(orc, depth, copy_streams):
     with unrelated kernels so that scatters lag behind copies. A copy that
     overwrote a device slot before the scatter reading it had finished, or a
     scatter that ran before its copy, would leave wrong bytes."""
-    t = synth.stress(n=3000, chunk=4096, dst_align=16)
+    t = synth.stress(n=4000, chunk=4096, dst_align=16)
     plan = ii.ii_plan(t)
+    assert not plan.pinned_link  # pinned blobs go through the ring too
     plan.set_ring(depth, 2, copy_streams)
     _, off = plan.tensors()
     blobs = [synth.blob(t.blob_bytes, seed=300 + i) for i in range(4)]
