@@ -174,8 +174,9 @@ void ii_plan_free(ii_plan_t* plan);
  *               ii_plan_prepare no load of a host blob does.
  *   host_blob   host address of blob byte 0. Pageable or pinned. Pageable
  *               blobs are read only during the call; a pinned blob
- *               (hipHostMalloc / ii_host_alloc) is read by DMA after the call
- *               returns and must stay valid and unchanged until `stream`
+ *               (hipHostMalloc / ii_host_alloc) is read after the call
+ *               returns, by DMA or by a kernel (ii_plan_pinned_link), and
+ *               must stay valid and unchanged until `stream`
  *               reaches the point after this call. A blob counts as pinned
  *               when its span [lo, hi) lies inside one pinned allocation;
  *               otherwise it is handled as pageable. Memory pinned by
@@ -187,9 +188,9 @@ void ii_plan_free(ii_plan_t* plan);
  *               dst_align[i]; the ranges [dst_ptrs[i], +nbytes[i]) must not
  *               overlap, and each must lie inside one device allocation or
  *               in pinned host memory that the device sees at the same
- *               address (checked, II_EINVAL; see ii_check_dst). Read during the call only; the memory they
- *               point to must stay allocated until `stream` passes this
- *               call.
+ *               address (checked, II_EINVAL; see ii_check_dst). Read during
+ *               the call only; the memory they point to must stay allocated
+ *               until `stream` passes this call.
  *   stream      HIP stream (0 = null stream). Writes into the destinations
  *               start only after all work already enqueued on `stream`, and
  *               complete before any work enqueued on `stream` afterwards.
@@ -237,8 +238,8 @@ int ii_load_file(ii_plan_t* plan, int fd, uint64_t file_bytes, void* const* dst_
  *                [dev_image + lo, + hi) must lie inside one device allocation
  *                or in pinned host memory that the device sees at the same
  *                address, as hipHostMalloc and ii_host_alloc give it (checked,
- *                II_EINVAL). From pinned host memory the kernel reads the blob over the host link
- *                itself: no ring and no copy engine, one launch of at most
+ *                II_EINVAL). From pinned host memory the kernel reads the
+ *                blob over the host link itself: no ring and no copy engine, one launch of at most
  *                256 workgroups (64 for most tables of 64 MiB and more) that
  *                walk the windows in order -- the lowest latency for small
  *                loads, and the link's rate for large ones. Kernels on other
@@ -348,6 +349,8 @@ int ii_switch(const ii_plan_t* plan_old, ii_plan_t* plan_new, void* arena, uint6
  * one chunk overlaps the scatter of another, and a slot whose next chunk
  * runs on another lane is handed over by an event. Each lane's first copy
  * of a load may run before the work the caller enqueued ahead of it.
+ * (A load that reads a pinned blob over the link has no lanes, and nothing of
+ * it runs ahead: ii_plan_pinned_link.)
  * Errors: II_EINVAL (out of range), II_EBUSY (ring already allocated, or a
  * load from host memory has run).
  */
@@ -481,17 +484,18 @@ int ii_plan_layout_tiles(const ii_plan_t* plan, uint64_t* num_tiles, uint32_t* s
  * the 128-byte lines that hold it come to at most 1.03 times
  * ii_plan_copy_bytes and the two lines the span begins and ends in. Both write the same bytes. 0 for a NULL plan. */
 int ii_plan_pinned_link(const ii_plan_t* plan);
-/* which of its two variants the resident-image kernel runs for a table of
- * this shape: 1 for the variant for tables of many small tensors (tiles that
- * one segment meets take a path without LDS staging, and every tile issues
- * all its loads before using any), chosen when at least II_LAYOUT_MIXED_PCT
- * percent (default 5; 0 = always, 101 = never) of the tiles meet three or
- * more segments, or when at least 3% meet two or more and most payload bytes
- * are phase-shifted (blob offset and layout position differ mod 16); 0 for
- * the other (fewer loads in flight, faster on large tables of large
- * tensors). Loads of at most 300 MiB run the former whatever the table
- * (unless 101), and an image in pinned host memory is read by a kernel of
- * its own. All write the same bytes. 0 for a NULL plan. */
+/* which of the two variants of the resident-image kernel the table's shape
+ * asks for. It decides for images in device memory of more than 300 MiB;
+ * smaller ones run the variant for many small tensors whatever this says
+ * (unless II_LAYOUT_MIXED_PCT=101), and an image in pinned host memory is read
+ * by a kernel of its own. 1 for the variant for tables of many small tensors
+ * (tiles that one segment meets take a path without LDS staging and issue one
+ * unit's loads at a time, the others issue all their loads before using any),
+ * chosen when at least II_LAYOUT_MIXED_PCT percent (default 5; 0 = always,
+ * 101 = never) of the tiles meet three or more segments, or when at least 3%
+ * meet two or more and most payload bytes are phase-shifted (blob offset and
+ * layout position differ mod 16); 0 for the other (faster on large tables of
+ * large tensors). All write the same bytes. 0 for a NULL plan. */
 int ii_plan_layout_mixed(const ii_plan_t* plan);
 /* name of row i as given to ii_plan ("" if none); valid while the plan lives */
 const char* ii_plan_tensor_name(const ii_plan_t* plan, size_t i);

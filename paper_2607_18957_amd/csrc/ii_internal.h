@@ -46,14 +46,15 @@ struct DstRange {
 };
 
 // Largest payload for which the image kernel runs its variant with more loads
-// in flight whatever the table. Up to about here image and destinations of a
-// load stay largely in the 256 MiB memory-side cache, whose latency, not a
-// stream's rate, bounds the kernel. Back-to-back loads, dense against mixed:
+// in flight whatever the table: where the two measured the same. Small loads
+// are bounded by latency (the least of them lie in the 256 MiB memory-side
+// cache, image and destinations), large ones by the rate of the stream, which
+// more loads in flight hold up. Back-to-back loads, dense against mixed:
 // transformer tables of 37 MB 11.3 and 10.2 us, 73 MB 19.8 and 18.8, 168 MB
 // 40.8 and 40.1, 293 MB 89.8 and 87.0, 335 MB 105.7 and 108.1, 566 MB 175 and
 // 184; one rank of four of 252 MB 79.7 and 73.4, 311 MB 94.8 and 92.0, 370 MB
 // 117.4 and 118.9. Below 20 MB a load takes the host longer than the device.
-constexpr uint64_t kCacheBytes = 300ull << 20;
+constexpr uint64_t kMixedBytes = 300ull << 20;
 
 // Largest payload of a dense table whose pinned blob is read over the link
 // (reads_over_link, runtime.hip, says why the line lies here).
@@ -159,8 +160,8 @@ struct ii_plan_s {
     // whether the image kernel runs its variant for tables of many small
     // tensors (more loads in flight; see the planner's rule)
     bool layout_mixed = false;
-    // whether an image load runs it for its size (see kCacheBytes)
-    bool layout_cached = false;
+    // whether an image load runs it for its size (see kMixedBytes)
+    bool layout_small = false;
     // whether an untraced load reads a pinned blob over the link
     bool pinned_link = false;
     // for the destination checks: the first non-empty tensor (n if none),

@@ -452,7 +452,7 @@ extern "C" int ii_plan(const ii_tensor_desc* table, size_t n, uint64_t chunk_byt
             const uint32_t pct = env_u32("II_LAYOUT_MIXED_PCT", 5, 0, 101);
             p->layout_mixed = pct <= 100 && (many * 100 >= (uint64_t)pct * G ||
                                              (two * 100 >= 3 * G && shifted * 2 >= bytes));
-            p->layout_cached = pct <= 100 && bytes <= kCacheBytes;
+            p->layout_small = pct <= 100 && bytes <= kMixedBytes;
             // see reads_over_link (256: the span's first and last line)
             p->pinned_link =
                 8 * p->row_bytes > bytes ||

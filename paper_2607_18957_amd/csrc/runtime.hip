@@ -1013,7 +1013,7 @@ static hipError_t scatter_image(const ii_plan_t* p, const uint8_t* image, const 
                                 uint64_t base, AllocInfo::Kind from, hipStream_t stream) {
     if (launch_injected()) return hipErrorLaunchFailure;
     const ImageKernel which = from == AllocInfo::kPinnedHost        ? ImageKernel::kLink
-                              : p->layout_mixed || p->layout_cached ? ImageKernel::kMixed
+                              : p->layout_mixed || p->layout_small ? ImageKernel::kMixed
                                                                     : ImageKernel::kDense;
     return launch_scatter_layout(image + p->lo, t, base, p->tile_bytes, which, stream);
 }

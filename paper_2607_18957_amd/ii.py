@@ -312,8 +312,8 @@ class Plan:
 
     @property
     def layout_mixed(self) -> bool:
-        """Whether the image kernel runs its variant for many small tensors
-        (see ii_plan_layout_mixed)."""
+        """Whether the table's shape asks for the image kernel's variant for
+        many small tensors (see ii_plan_layout_mixed)."""
         return bool(_lib.ii_plan_layout_mixed(self.handle))
 
     @property
