@@ -251,10 +251,10 @@ int ii_load_file(ii_plan_t* plan, int fd, uint64_t file_bytes, void* const* dst_
  *                it. The caller keeps the image and destinations alive
  *                until the stream passes this call.
  * Under stream capture (once a call outside one has allocated the plan's
- * tables): the graph reads those tables, so the plan must outlive it; and
- * where the destinations are not one arena of the plan's layout, it may read
- * the rows of the plan's last load of that kind, so no other destinations of
- * that kind may be loaded between capture and replay.
+ * tables, with destinations of the same kind): the graph reads those tables,
+ * so the plan must outlive it. Where the destinations are not one arena of the
+ * plan's layout, every replay forms their rows in memory of the plan that its
+ * other loads of that kind use too: the caller orders replays and such loads.
  * Errors: as ii_load.
  */
 int ii_load_device(ii_plan_t* plan, const void* dev_image, uint64_t image_bytes,

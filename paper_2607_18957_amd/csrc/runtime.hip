@@ -148,6 +148,7 @@ struct Runtime {
     // records it again, so it covers all of them, whatever their streams.
     hipEvent_t lown_idle = nullptr;
     bool lown_used = false;
+    bool lown_replayed = false;  // a graph may write d_lown at any time
     bool image_used = false;              // an image kernel may be in flight
     // the ring's rows: read and written on the lanes, joined by lane 0
     hipEvent_t segs_uploaded = nullptr;   // after the last read of h_segs / h_psegs
@@ -691,16 +692,18 @@ static int ensure_own_rows(ii_plan_t* p, bool staged) {
 // Make d_lown hold destinations that are not one arena for the work enqueued
 // next on `s`: ordered after the work that formed or read its rows, on
 // whichever stream (a wait for an event of the same stream does nothing).
-// Rows formed while `s` is being captured are formed when the graph runs, so
-// no later load may count on them; and a capture cannot wait for an event of
-// the streams outside it.
+// A capture cannot wait for an event of the streams outside it, and what it
+// holds runs at some later time, so a captured load forms its rows in the
+// graph, at every replay, whatever rows are there; and from then on no load
+// may count on rows formed before it.
 static int image_own_rows(ii_plan_t* p, const uint64_t* dst, hipStream_t s, bool captured) {
     Runtime* r = p->rt;
     const bool few = fits_by_value(p, true), staged = !few && !captured;
     int rc = ensure_own_rows(p, staged);
     if (rc) return rc;
     if (r->lown_used && !captured) II_HIP(hipStreamWaitEvent(s, r->lown_idle, 0));
-    if (r->lown_ok) return II_OK;
+    if (captured) r->lown_replayed = true;
+    if (r->lown_ok && !r->lown_replayed) return II_OK;
     // Destinations too many for a few launches' arguments are staged in pinned
     // memory, so that the call does not wait for the work ahead on `s`, and
     // apart from p->ldst(), which a captured ii_load_device_noalloc of as many
@@ -727,7 +730,7 @@ static int image_own_rows(ii_plan_t* p, const uint64_t* dst, hipStream_t s, bool
         II_HIP(hipEventRecord(r->lown_sent, s));
         r->lown_staged = true;
     }
-    r->lown_ok = !captured;
+    r->lown_ok = true;
     return II_OK;
 }
 

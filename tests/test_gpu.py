@@ -629,7 +629,8 @@ def test_own_destinations_across_streams(orc, n):
             arena.fill_(0xA5)
         torch.cuda.synchronize()
 
-    # rows formed in a captured load exist only once the graph has run
+    # A captured load's rows are formed by its replays, whatever rows were there
+    # when it was captured or have come since.
     g = torch.cuda.CUDAGraph()
     with torch.cuda.graph(g):
         ii.ii_load_device(plan, image, sets[2][2], torch.cuda.current_stream(DEV))
@@ -644,6 +645,26 @@ def test_own_destinations_across_streams(orc, n):
         torch.cuda.synchronize()
         ii.ii_load_device(plan, image, sets[2][2], a)
         check([2])
+
+    # the same where its rows were there when it was captured, and other
+    # destinations are loaded between the replays
+    ii.ii_load_device(plan, image, sets[0][2], a)
+    g2 = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g2):
+        ii.ii_load_device(plan, image, sets[0][2], torch.cuda.current_stream(DEV))
+    torch.cuda.synchronize()
+    for _ in range(3):
+        for _, arena, _ in sets:
+            arena.fill_(0xA5)
+        ii.ii_load_device(plan, image, sets[1][2])
+        g2.replay()
+        ii.ii_load_device(plan, image, sets[1][2])
+        g.replay()
+        check([0, 1, 2])
+        sets[1][1].fill_(0xA5)
+        torch.cuda.synchronize()
+        ii.ii_load_device(plan, image, sets[1][2], b)
+        check([1])
     plan.free()
 
 
