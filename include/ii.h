@@ -281,12 +281,9 @@ int ii_load_device(ii_plan_t* plan, const void* dev_image, uint64_t image_bytes,
  * safe, calls that overlap on different streams of one GPU race (the later
  * upload may overwrite tables an earlier kernel still reads) and must be
  * ordered by the caller.
- * Under stream capture (replays are calls as above): the graph uploads from
- * the plan's own memory again at every replay, so the plan must live as long
- * as the graph; and a table of more than 512 segments whose destinations are
- * not one arena of the plan's layout goes, at replay, to the destinations of
- * the plan's last call of ii_load_device_noalloc of that kind, so none with
- * other destinations may come between.
+ * Under stream capture (replays are calls as above): the graph may upload
+ * from the plan's own memory again at every replay, so the plan must live as
+ * long as the graph. It keeps the destinations of the captured call.
  * Errors: as ii_load_device, plus II_ESCRATCH.
  */
 int ii_load_device_noalloc(ii_plan_t* plan, const void* dev_image, uint64_t image_bytes,

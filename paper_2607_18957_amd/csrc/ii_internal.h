@@ -138,8 +138,9 @@ struct ii_plan_s {
     std::vector<uint32_t> lseg;
     // what the device forms the kernel's rows from, in the order it is
     // uploaded in, so that one copy takes all: a destination per segment
-    // (written by ii_load_device_noalloc, which allocates nothing; by other
-    // loads only where they go as kernel arguments), a LayoutRow and a length
+    // (written by ii_load_device_noalloc, which allocates nothing, and by
+    // loads whose destinations go as kernel arguments), a LayoutRow and a
+    // length
     std::vector<uint64_t> lstage;
     uint64_t* ldst() { return lstage.data(); }
     const uint64_t* ldst() const { return lstage.data(); }

@@ -331,6 +331,15 @@ static int ensure_ring_tables(ii_plan_t* p) {
     return II_OK;
 }
 
+static bool capturing(hipStream_t s) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return st != hipStreamCaptureStatusNone;
+}
+
 // Where each of the image kernel's tables sits in a block of device memory
 // (offsets 256-aligned): rows, tiles and windows up to `end`, then what the
 // rows are formed from.
@@ -404,9 +413,10 @@ static int put_rows(const ii_plan_t* p, const uint64_t* words, uint8_t* stage, L
     return II_OK;
 }
 
-// Upload and form all of a plan's tables in the block at `at`.
+// Upload and form all of a plan's tables in the block at `at` (by_value: see
+// put_rows).
 static int put_layout(const ii_plan_t* p, uint8_t* at, const LayoutBlock& l, bool own_dst,
-                      hipStream_t s) {
+                      bool by_value, hipStream_t s) {
     const bool listed = !p->lwin.empty();
     if (listed) {
         II_HIP(h2d(at + l.tiles, p->ltiles.data(), p->ltiles.size() * sizeof(TileDev), s));
@@ -414,8 +424,8 @@ static int put_layout(const ii_plan_t* p, uint8_t* at, const LayoutBlock& l, boo
     }
     return put_rows(p, p->lstage.data() + (own_dst ? 0 : p->lseg.size()), at + l.stage,
                     reinterpret_cast<LayoutSeg*>(at + l.rows),
-                    listed ? nullptr : reinterpret_cast<TileDev*>(at + l.tiles), own_dst,
-                    fits_by_value(p, own_dst), s);
+                    listed ? nullptr : reinterpret_cast<TileDev*>(at + l.tiles), own_dst, by_value,
+                    s);
 }
 
 static int ensure_layout_tables(ii_plan_t* p) {
@@ -423,7 +433,7 @@ static int ensure_layout_tables(ii_plan_t* p) {
     if (r->layout_ready || p->lseg.empty()) return II_OK;
     const LayoutBlock l = layout_block(p);
     if (!r->d_layout) II_HIP(dev_alloc(&r->d_layout, l.all));
-    const int rc = put_layout(p, r->d_layout, l, false, nullptr);
+    const int rc = put_layout(p, r->d_layout, l, false, fits_by_value(p, false), nullptr);
     if (rc) return rc;
     II_HIP(hipStreamSynchronize(nullptr));
     r->layout_ready = true;
@@ -667,15 +677,6 @@ static void layout_dst(const ii_plan_t* p, const uint64_t* dst, uint64_t* out) {
     }
 }
 
-static bool capturing(hipStream_t s) {
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
-    }
-    return st != hipStreamCaptureStatusNone;
-}
-
 // Allocate the rows of destinations that are not one arena, and the pinned
 // staging for them if `staged`.
 static int ensure_own_rows(ii_plan_t* p, bool staged) {
@@ -705,10 +706,9 @@ static int image_own_rows(ii_plan_t* p, const uint64_t* dst, hipStream_t s, bool
     if (captured) r->lown_replayed = true;
     if (r->lown_ok && !r->lown_replayed) return II_OK;
     // Destinations too many for a few launches' arguments are staged in pinned
-    // memory, so that the call does not wait for the work ahead on `s`, and
-    // apart from p->ldst(), which a captured ii_load_device_noalloc of as many
-    // reads again at replay. A captured load's go as arguments of as many
-    // launches as it takes: the graph keeps those.
+    // memory, so that the call does not wait for the work ahead on `s`. A
+    // captured load's go as arguments of as many launches as it takes: the
+    // graph keeps those.
     std::vector<uint64_t> copy;
     uint64_t* words = p->ldst();
     if (staged) {
@@ -1160,7 +1160,10 @@ static int run_device_noalloc(ii_plan_t* p, const uint8_t* image, const uint64_t
     if (rc) return rc;
     const LayoutBlock l = layout_block(p);
     if (!to.arena) layout_dst(p, dst, p->ldst());
-    rc = put_layout(p, ws, l, !to.arena, stream);
+    // a graph uploads again at every replay what an upload read: fine for the
+    // plan's tables, which never change; destinations it keeps as arguments
+    const bool by_value = fits_by_value(p, !to.arena) || (!to.arena && capturing(stream));
+    rc = put_layout(p, ws, l, !to.arena, by_value, stream);
     if (rc) return rc;
     const LayoutTable t = layout_table(p, ws, l, reinterpret_cast<const LayoutSeg*>(ws + l.rows));
     II_HIP(scatter_image(p, image, t, to.base, info.kind, stream));

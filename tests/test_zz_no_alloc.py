@@ -137,7 +137,7 @@ def test_noalloc_table_sizes(orc, n):
 def test_noalloc_captured_then_other_loads(orc, n, gap):
     """A captured call goes to its own destinations at every replay, whatever
     other loads of the plan did in between: ii_load_device and the call
-    itself into an arena, ii_load_device into destinations of their own."""
+    itself into an arena and into destinations of their own."""
     t = synth.stress(n=n, chunk=1 << 18)
     plan = ii.ii_plan(t)
     _, off = plan.tensors()
@@ -165,6 +165,7 @@ def test_noalloc_captured_then_other_loads(orc, n, gap):
             ii.ii_load_device(plan, image, other[1])
             ii.ii_load_device(plan, image, arena[1])
             ii.ii_load_device_noalloc(plan, image, arena[1])
+            ii.ii_load_device_noalloc(plan, image, other[1])
         torch.cuda.synchronize()
         g.replay()
         torch.cuda.synchronize()
