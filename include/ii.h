@@ -477,7 +477,7 @@ int ii_plan_layout_tiles(const ii_plan_t* plan, uint64_t* num_tiles, uint32_t* s
  * the blob at its host address) is one launch that reads the blob over the
  * host link, 0 if it runs the chunk pipeline: 1 when more than an eighth of the
  * payload lies in chunks that the pipeline would move row by row (by 2-D
- * copies, or gathered on the host), or when the payload is at most 32 MiB and
+ * copies, or gathered on the host), or when the payload is at most 64 MiB and
  * the 128-byte lines that hold it come to at most 1.03 times
  * ii_plan_copy_bytes and the two lines the span begins and ends in. Both write the same bytes. 0 for a NULL plan. */
 int ii_plan_pinned_link(const ii_plan_t* plan);

@@ -58,7 +58,7 @@ constexpr uint64_t kMixedBytes = 300ull << 20;
 
 // Largest payload of a dense table whose pinned blob is read over the link
 // (reads_over_link, runtime.hip, says why the line lies here).
-constexpr uint64_t kLinkBytes = 32ull << 20;
+constexpr uint64_t kLinkBytes = 64ull << 20;
 
 // Static device workspace of ii_load_device_noalloc (runtime.hip): the
 // kernel's tables, and after them what the segments' rows are formed from

@@ -1079,13 +1079,14 @@ static int run_device(ii_plan_t* p, const uint8_t* image, const uint64_t* dst, h
 //     us; 353 -> 218 when each is waited for);
 //   others of at most kLinkBytes: the pipeline's first copy and last scatter,
 //     its hand-overs and the copy engines' start-up are then a sizeable part
-//     (17 MB in 4 MiB chunks: 377 -> 312 us on an idle stream, 707 and more ->
-//     301 back to back; 31 MB: 663 -> 568 and 1395 -> 558), and the copies that
-//     run ahead save no more than the load's own time (behind other work 160
-//     and 434 us against 303 and 559). Larger ones gain 3 to 8% on an idle
-//     stream (82 MB 1569 -> 1447 us, 327 MB 5.89 -> 5.73 ms) and would lose up
-//     to depth * chunk_bytes of overlap behind other work (327 MB in 64 MiB
-//     chunks: 2.35 ms -> 5.70 ms). Where small tensors lie scattered the
+//     (in 4 MiB chunks, on an idle stream and back to back: 17 MB 377 -> 312 us,
+//     707 and more -> 301; 31 MB 663 -> 568, 1395 -> 558; 57 MB 1127 -> 1013,
+//     1846 -> 1005), more than the copies ahead save in small chunks (behind
+//     other work 160, 434 and 896 us against 303, 559 and 1004), and in large
+//     ones those save at most the load's 1.2 ms (57 MB in 16 MiB chunks: 208
+//     against 1004). Larger ones gain less on an idle stream (82 MB 1528 -> 1447
+//     us, 327 MB 5.89 -> 5.73 ms) and would lose up to depth * chunk_bytes of
+//     overlap (327 MB in 64 MiB chunks: 2.35 ms -> 5.70 ms). Where small tensors lie scattered the
 //     pipeline is ahead at any size: the link carries whole 128-byte lines, and
 //     where those come to more than 1.03 times what the pipeline copies (and the
 //     two at the span's ends, which weigh in tables of some 10 KB) it is

@@ -437,7 +437,7 @@ _ROUTES = {
     "tiny": (lambda: synth.tiny(), True),
     "tiny-shard": (lambda: synth.tiny_tp(1, 4), True),
     "scattered": (lambda: synth.stress(n=3000, lo_bytes=64, hi_bytes=512), False),
-    "above-32M": (lambda: synth.transformer("m", 4, 512, 2048, 512, 8192, chunk=16 << 20), False),
+    "above-64M": (lambda: synth.transformer("m", 4, 768, 2048, 768, 8192, chunk=16 << 20), False),
 }
 
 
@@ -677,7 +677,7 @@ def test_ring_race_stress(orc, depth, copy_streams):
     with unrelated kernels so that scatters lag behind copies. A copy that
     overwrote a device slot before the scatter reading it had finished, or a
     scatter that ran before its copy, would leave wrong bytes."""
-    t = synth.stress(n=4000, chunk=4096, dst_align=16)
+    t = synth.stress(n=7500, chunk=4096, dst_align=16)
     plan = ii.ii_plan(t)
     assert not plan.pinned_link  # pinned blobs go through the ring too
     plan.set_ring(depth, 2, copy_streams)

@@ -391,7 +391,7 @@ def _expected_pinned_link(plan, op, s, chunk):
     rows, total = _expected_row_share(op)
     if 8 * rows > total:
         return True
-    return (total <= 32 << 20
+    return (total <= 64 << 20
             and 100 * _expected_line_bytes(plan, s, lo, chunk) <= 103 * plan.copy_bytes + 25600)
 
 
@@ -485,8 +485,8 @@ _LINK_CASES = {
     # dense: by size, whatever the chunks
     "dense-17M": (lambda: synth.tiny(), True),
     "dense-17M-in-257-chunks": (lambda: synth.tiny(chunk=64 << 10), True),
-    "dense-at-the-limit": (lambda: oracle_pins._u8_table([31 * M, M], [0, 31 * M], [1, 1]), True),
-    "dense-above-it": (lambda: oracle_pins._u8_table([31 * M, M + 1], [0, 31 * M], [1, 1]), False),
+    "dense-at-the-limit": (lambda: oracle_pins._u8_table([63 * M, M], [0, 63 * M], [1, 1]), True),
+    "dense-above-it": (lambda: oracle_pins._u8_table([63 * M, M + 1], [0, 63 * M], [1, 1]), False),
     "dense-3G-in-12-chunks":
         (lambda: synth.transformer("m", 16, 2048, 8192, 512, 128256, chunk=256 * M), False),
     # ... and by the source lines of small scattered tensors
